@@ -23,10 +23,10 @@ hipError_t launch_append(const AppendArgs &a, hipStream_t stream);
 hipError_t launch_gather(const GatherArgs &a, hipStream_t stream);
 hipError_t launch_decode(const DecodeArgs &a, int grid, uint32_t mask, hipStream_t stream, hipEvent_t ev0,
                          hipEvent_t ev1);
-hipError_t launch_decode_wide(const DecodeArgs &a, int grid, int variant, hipStream_t stream, hipEvent_t ev0,
+hipError_t launch_decode_mla(const DecodeArgs &a, int grid, int variant, hipStream_t stream, hipEvent_t ev0,
                               hipEvent_t ev1);
 int decode_wgs_per_cu(uint32_t mask);
-int narrow_streams(int variant);
+int matrix_streams(int variant);
 hipError_t launch_merge(const MergeArgs &a, hipStream_t stream);
 hipError_t launch_stack_push(const StackPushArgs &a, hipStream_t stream);
 hipError_t scratch_device_address(int device, void **out);
@@ -788,10 +788,10 @@ constexpr int32_t kMatrixFirst = 16;
 // Matrix-core variant for a model, or -1 when none fits its geometry. The
 // matrix path serves models whose query heads share a KV head in groups of
 // 8 or more (the MLA latent head, MQA, GQA), where the per-KV-head work is a
-// contraction over the group: the narrow variants (8-32 heads) stream
-// wave-private slices of 16 (MLA) or 32 (head_dim 128) tokens, the wide ones
-// (64-128 heads) 32-token tiles shared by the workgroup. Pages must hold a
-// whole number of slices or tiles.
+// contraction over the group: the narrow variants (8-32 heads) stream slices
+// of 16 (MLA) or 32 (head_dim 128) tokens through pairs of waves, the others
+// (64-128 heads) 32-token tiles shared by four or eight waves. Pages must
+// hold a whole number of slices or tiles.
 int32_t matrix_variant(const Geom &g, int32_t P) {
   if (g.kind == kMLA && g.latent == 512 && g.rope == 64) {
     if (g.g == 16 && P % 16 == 0) return kM_MLA_G16;
@@ -809,12 +809,12 @@ int32_t matrix_variant(const Geom &g, int32_t P) {
   return -1;
 }
 
-// Work units per KV range of a request: the narrow matrix kernel takes one
+// Work units per KV range of a request: the eight-wave matrix kernels take one
 // KV head per token stream at once when the model's KV heads are a multiple
 // of its stream count; otherwise every KV head (times its head blocks) is a
 // unit of its own.
 int32_t units_per_range(const Geom &g, const GeomK &k) {
-  const int ns = narrow_streams(k.variant);
+  const int ns = matrix_streams(k.variant);
   if (ns > 0 && g.hkv % ns == 0) return g.hkv / ns;
   return g.hkv * k.nb;
 }
@@ -974,11 +974,17 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
   }
   if (qo > 0xFFFFFFFFull || oo > 0xFFFFFFFFull) return fail(CP_EINVAL, "batch too large");
   // kernel family: vector variants share a launch, narrow matrix variants
-  // share another, and each wide variant has a kernel of its own
+  // share another, head-owner ones a third, and 128-head MLA has a kernel of
+  // its own
   auto wclass = [&](int32_t i) {
     const int v = gk[model_of(i)].variant;
-    // (launch classes: vector, narrow matrix, small-group vector, each wide variant)
-    return is_wide_variant(v) ? v : v >= kMatrixFirst ? 1 : (v >= kS_G1_D64 && v <= kS_G4_D128) ? 2 : 0;
+    // (launch classes: vector, narrow matrix, small-group vector, head-owner
+    // matrix, 128-head MLA)
+    return is_mla_wide(v)                               ? v
+           : is_many_heads(v)                           ? 3
+           : v >= kMatrixFirst                          ? 1
+           : (v >= kS_G1_D64 && v <= kS_G4_D128)        ? 2
+                                                        : 0;
   };
 
   // Launch groups: requests whose kernels share a workgroup size, at most
@@ -1016,7 +1022,7 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
   cost_prefix.assign(n, 0);
   for (int32_t i = 0; i < n; ++i) hblk[i] = units_per_range(p->st.model(model_of(i)), gk[model_of(i)]);
   for (Group &g : groups) {
-    const bool wide = g.mask && is_wide_variant(__builtin_ctz(g.mask));
+    const bool wide = g.mask && is_mla_wide(__builtin_ctz(g.mask));
     const int wgs = wide ? 1 : decode_wgs_per_cu(g.mask);
     const int64_t slots = (int64_t)p->num_cus * wgs;
     if (o.schedule == CP_SCHED_BALANCED) {
@@ -1068,7 +1074,7 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
       std::vector<int32_t> hb;
       for (int32_t i : g.idx) {
         const int32_t v = gk[model_of(i)].variant;
-        all_wide = all_wide && is_wide_variant(v);
+        all_wide = all_wide && is_many_heads(v);
         any_matrix = any_matrix || v >= kMatrixFirst;
         pin.push_back(PlanIn{model_of(i), pl->attend[i]});
         hb.push_back(hblk[i]);
@@ -1195,7 +1201,7 @@ cp_status launch_plan(cp_pool *p, const DecodePlan &pl, int32_t n, const int32_t
     const int v0 = __builtin_ctz(g.mask);
     const hipEvent_t ev0 = gi == 0 ? (hipEvent_t)o.ev_begin : nullptr;
     const hipEvent_t ev1 = gi + 1 == pl.groups.size() ? (hipEvent_t)o.ev_end : nullptr;
-    hipError_t e = is_wide_variant(v0) ? launch_decode_wide(a, g.grid, v0, s, ev0, ev1)
+    hipError_t e = is_mla_wide(v0) ? launch_decode_mla(a, g.grid, v0, s, ev0, ev1)
                                        : launch_decode(a, g.grid, g.mask, s, ev0, ev1);
     if (e != hipSuccess) return hip_fail(e, "decode launch");
   }

@@ -1,5 +1,5 @@
 // Pieces shared by the matrix-core decode kernels (decode_narrow.h,
-// decode_wide.h): operand vector types, direct HBM -> LDS loads with the
+// decode_heads.h, decode_mla.h): operand vector types, direct HBM -> LDS loads with the
 // non-temporal policy, vmcnt waits, and constants of the online softmax.
 #pragma once
 

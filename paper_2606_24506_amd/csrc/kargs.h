@@ -38,15 +38,17 @@ constexpr uint32_t kPieceFixedCost = 40;
 //     1, 2 or 4 query heads per KV head and head_dim 64 or 128.
 //   Narrow matrix path (16, 17, 19, 20, 23): 8, 16 or 32 query heads per KV
 //     head (MLA latent head, or head_dim 128).
-//   Wide matrix path (18, 21, 22): 64 or 128 query heads per KV head; its
-//     own kernel (one workgroup per CU, scores split by heads, P.V by
-//     columns).
+//   Head-owner matrix path (21, 22): 64 or 128 query heads per KV head with
+//     head_dim 128.
+//   128-head MLA (18): its own kernel (score waves and P.V waves).
 enum : int32_t {
   kV16x8 = 0, kV16x4, kV16x2, kV16x1, kV8x8, kV8x4, kV8x2, kV8x1,
   kS_G1_D64 = 8, kS_G2_D64, kS_G4_D64, kS_G1_D128, kS_G2_D128, kS_G4_D128,
   kM_MLA_G16 = 16, kM_MLA_G32, kM_MLA_G128, kM_D128_G16, kM_D128_G32, kM_D128_G64, kM_D128_G128, kM_D128_G8
 };
-constexpr bool is_wide_variant(int v) { return v == kM_MLA_G128 || v == kM_D128_G64 || v == kM_D128_G128; }
+constexpr bool is_mla_wide(int v) { return v == kM_MLA_G128; }
+// Variants with 64 or more heads per KV head, whose partials are large.
+constexpr bool is_many_heads(int v) { return v == kM_MLA_G128 || v == kM_D128_G64 || v == kM_D128_G128; }
 
 // One piece of decode work: pages [pg_begin, pg_end) of a request, for one
 // head block, writing partial slot `slot` when the request is split; model

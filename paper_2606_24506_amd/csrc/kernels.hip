@@ -13,6 +13,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "decode_heads.h"
 #include "decode_mfma.h"
 #include "decode_narrow.h"
 #include "decode_small.h"
@@ -285,6 +286,13 @@ template <int V>
 using NarrowCfgOf = NarrowCfg<NarrowVar<V>::G, NarrowVar<V>::DK, NarrowVar<V>::DV, NarrowVar<V>::MLA, NarrowVar<V>::TW,
                               kNarrowWaves, NarrowVar<V>::SHARE, NarrowVar<V>::NSLOT>;
 
+// Head-owner variants: query heads per KV head and head_dim.
+template <int V> struct HeadsVar;
+template <> struct HeadsVar<kM_D128_G64> { static constexpr int G = 64, D = 128; };
+template <> struct HeadsVar<kM_D128_G128> { static constexpr int G = 128, D = 128; };
+template <int V>
+using HeadsCfgOf = HeadsCfg<HeadsVar<V>::G, HeadsVar<V>::D>;
+
 template <int V>
 constexpr int narrow_lds() { return NarrowCfgOf<V>::LDS; }
 
@@ -312,6 +320,9 @@ constexpr int kernel_lds_bytes(uint32_t mask) {
 #define CP_B(V) if (has(mask, V) && narrow_lds<V>() > b) b = narrow_lds<V>();
   CP_B(kM_MLA_G16) CP_B(kM_MLA_G32) CP_B(kM_D128_G8) CP_B(kM_D128_G16) CP_B(kM_D128_G32)
 #undef CP_B
+#define CP_H(V) if (has(mask, V) && HeadsCfgOf<V>::LDS > b) b = HeadsCfgOf<V>::LDS;
+  CP_H(kM_D128_G64) CP_H(kM_D128_G128)
+#undef CP_H
   return b;
 }
 
@@ -348,6 +359,15 @@ __device__ __forceinline__ void run_seg(const DecodeArgs &a, const DecReq &rq, c
   }
   CP_NCASE(kM_MLA_G16) CP_NCASE(kM_MLA_G32) CP_NCASE(kM_D128_G8) CP_NCASE(kM_D128_G16) CP_NCASE(kM_D128_G32)
 #undef CP_NCASE
+#define CP_HCASE(V)                                                      \
+  if constexpr (has(MASK, V)) {                                          \
+    if (gm.variant == V) {                                               \
+      heads_unit<HeadsVar<V>::G, HeadsVar<V>::D>(a, gm, rq, sg, lds);    \
+      return;                                                            \
+    }                                                                    \
+  }
+  CP_HCASE(kM_D128_G64) CP_HCASE(kM_D128_G128)
+#undef CP_HCASE
 }
 
 // One kernel per variant set of the narrow family; four waves per
@@ -370,6 +390,7 @@ constexpr uint32_t vbit(int v) { return 1u << v; }
 // The variant sets the host launches together: each single variant, and
 // the mixed MLA-16 / MQA-32 / GQA-8 batch.
 constexpr uint32_t kMixedSmall = vbit(kM_MLA_G16) | vbit(kM_D128_G32) | vbit(kM_D128_G8);
+constexpr uint32_t kAllHeads = vbit(kM_D128_G64) | vbit(kM_D128_G128);
 constexpr uint32_t kAllNarrow =
     vbit(kM_MLA_G16) | vbit(kM_MLA_G32) | vbit(kM_D128_G16) | vbit(kM_D128_G32) | vbit(kM_D128_G8);
 
@@ -390,6 +411,7 @@ hipError_t launch_decode(const DecodeArgs &a, int grid, uint32_t mask, hipStream
     CP_L(vbit(kM_MLA_G16)) CP_L(vbit(kM_MLA_G32)) CP_L(vbit(kM_D128_G16)) CP_L(vbit(kM_D128_G32))
     CP_L(vbit(kM_D128_G8))
     CP_L(kMixedSmall)
+    CP_L(vbit(kM_D128_G64)) CP_L(vbit(kM_D128_G128)) CP_L(kAllHeads)
     CP_L(vbit(kS_G1_D64)) CP_L(vbit(kS_G2_D64)) CP_L(vbit(kS_G4_D64)) CP_L(vbit(kS_G1_D128)) CP_L(vbit(kS_G2_D128))
     CP_L(vbit(kS_G4_D128))
     default: break;
@@ -410,15 +432,17 @@ hipError_t launch_decode(const DecodeArgs &a, int grid, uint32_t mask, hipStream
   return hipErrorInvalidValue;
 }
 
-// Token streams of the narrow kernel for a variant (KV heads a unit covers
-// when they split across streams).
-int narrow_streams(int variant) {
+// Token streams of the workgroup for a matrix variant (KV heads a unit
+// covers when they split across streams).
+int matrix_streams(int variant) {
   switch (variant) {
     case kM_MLA_G16: return NarrowCfgOf<kM_MLA_G16>::NSTREAM;
     case kM_MLA_G32: return NarrowCfgOf<kM_MLA_G32>::NSTREAM;
     case kM_D128_G8: return NarrowCfgOf<kM_D128_G8>::NSTREAM;
     case kM_D128_G16: return NarrowCfgOf<kM_D128_G16>::NSTREAM;
     case kM_D128_G32: return NarrowCfgOf<kM_D128_G32>::NSTREAM;
+    case kM_D128_G64: return HeadsCfgOf<kM_D128_G64>::NSTREAM;
+    case kM_D128_G128: return HeadsCfgOf<kM_D128_G128>::NSTREAM;
     default: return 0;
   }
 }
@@ -433,6 +457,9 @@ int decode_wgs_per_cu(uint32_t mask) {
 #define CP_B(V) if (has(mask, V) && narrow_lds<V>() > b) b = narrow_lds<V>();
   CP_B(kM_MLA_G16) CP_B(kM_MLA_G32) CP_B(kM_D128_G8) CP_B(kM_D128_G16) CP_B(kM_D128_G32)
 #undef CP_B
+#define CP_H(V) if (has(mask, V) && HeadsCfgOf<V>::LDS > b) b = HeadsCfgOf<V>::LDS;
+  CP_H(kM_D128_G64) CP_H(kM_D128_G128)
+#undef CP_H
   const int per = (160 * 1024) / (b + 64);
   return per < 1 ? 1 : per;
 }
