@@ -302,7 +302,8 @@ cp_status cp_attn_decode(cp_pool *pool, int32_t n, const int32_t *req_ids, const
                          void *hip_stream);
 
 typedef enum {
-  CP_PATH_AUTO = 0, /* matrix cores where many query heads share a KV head, vector otherwise */
+  CP_PATH_AUTO = 0, /* matrix cores where a kernel for the geometry exists (P kept to 17 bits or, with 8, 16, 32, 64 or
+                       128 query heads per KV head, to bf16), vector otherwise */
   CP_PATH_VALU = 1, /* force the vector (wavefront-reduction) kernel for every model */
   CP_PATH_MFMA = 2  /* force the matrix-core kernel for every model */
 } cp_path;

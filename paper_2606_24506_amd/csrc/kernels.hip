@@ -17,6 +17,7 @@
 #include "decode_mfma.h"
 #include "decode_narrow.h"
 #include "decode_small.h"
+#include "decode_stream.h"
 #include "device_common.h"
 #include "kargs.h"
 #include "schedule.h"
@@ -323,6 +324,8 @@ constexpr int kernel_lds_bytes(uint32_t mask) {
 #define CP_H(V) if (has(mask, V) && HeadsCfgOf<V>::LDS > b) b = HeadsCfgOf<V>::LDS;
   CP_H(kM_D128_G64) CP_H(kM_D128_G128)
 #undef CP_H
+  if (has(mask, kT_D64) && StreamCfg<64>::LDS > b) b = StreamCfg<64>::LDS;
+  if (has(mask, kT_D128) && StreamCfg<128>::LDS > b) b = StreamCfg<128>::LDS;
   return b;
 }
 
@@ -368,6 +371,18 @@ __device__ __forceinline__ void run_seg(const DecodeArgs &a, const DecReq &rq, c
   }
   CP_HCASE(kM_D128_G64) CP_HCASE(kM_D128_G128)
 #undef CP_HCASE
+  if constexpr (has(MASK, kT_D64)) {
+    if (gm.variant == kT_D64) {
+      stream_unit<64>(a, gm, rq, sg, lds);
+      return;
+    }
+  }
+  if constexpr (has(MASK, kT_D128)) {
+    if (gm.variant == kT_D128) {
+      stream_unit<128>(a, gm, rq, sg, lds);
+      return;
+    }
+  }
 }
 
 // One kernel per variant set of the narrow family; four waves per
@@ -412,6 +427,7 @@ hipError_t launch_decode(const DecodeArgs &a, int grid, uint32_t mask, hipStream
     CP_L(vbit(kM_D128_G8))
     CP_L(kMixedSmall)
     CP_L(vbit(kM_D128_G64)) CP_L(vbit(kM_D128_G128)) CP_L(kAllHeads)
+    CP_L(vbit(kT_D64)) CP_L(vbit(kT_D128)) CP_L(vbit(kT_D64) | vbit(kT_D128))
     CP_L(vbit(kS_G1_D64)) CP_L(vbit(kS_G2_D64)) CP_L(vbit(kS_G4_D64)) CP_L(vbit(kS_G1_D128)) CP_L(vbit(kS_G2_D128))
     CP_L(vbit(kS_G4_D128))
     default: break;
@@ -460,6 +476,8 @@ int decode_wgs_per_cu(uint32_t mask) {
 #define CP_H(V) if (has(mask, V) && HeadsCfgOf<V>::LDS > b) b = HeadsCfgOf<V>::LDS;
   CP_H(kM_D128_G64) CP_H(kM_D128_G128)
 #undef CP_H
+  if (has(mask, kT_D64) && StreamCfg<64>::LDS > b) b = StreamCfg<64>::LDS;
+  if (has(mask, kT_D128) && StreamCfg<128>::LDS > b) b = StreamCfg<128>::LDS;
   const int per = (160 * 1024) / (b + 64);
   return per < 1 ? 1 : per;
 }

@@ -1,5 +1,5 @@
-"""GPU parity of the kernels that own whole query heads, over the head counts
-they serve: 32-token tiles (contexts of one token, one short of and one past
+"""GPU parity of the kernels whose waves own whole query heads, over the head
+counts they serve: 16- and 32-token tiles (contexts of one token, one short of and one past
 a tile, several tiles, several batches of page-table entries), KV heads that
 split over the token streams of a workgroup and KV heads that do not, pages
 of one tile and more, and scores that climb so that the softmax reference
@@ -82,3 +82,50 @@ def test_many_heads_per_kv_head(heads, kv, page_tokens, schedule, splits):
 def test_many_heads_long_pieces():
     """Unsplit pieces of more than 64 and 128 pages, and two variants in one launch."""
     run([(gqa(64, 1), 2100), (gqa(128, 1), 4300), (gqa(128, 2), 2081)], 32, QUE, 1)
+
+
+# groups of every kind: 1-4 heads, odd ones, a full unit of 16, two units and
+# more; KV heads that fill the eight streams, share them, or are odd
+@pytest.mark.parametrize("heads,kv,d", [(8, 8, 64), (16, 4, 64), (40, 8, 64), (6, 1, 64), (32, 8, 128), (16, 16, 128),
+                                        (21, 3, 128), (28, 4, 128), (30, 6, 128), (12, 1, 128), (40, 2, 128),
+                                        (100, 1, 128)])
+@pytest.mark.parametrize("page_tokens,schedule,splits", [(64, BAL, 0), (32, QUE, 1), (96, QUE, 3)])
+def test_any_group(heads, kv, d, page_tokens, schedule, splits):
+    print(f"[case] {heads}:{kv} d{d} P{page_tokens} sched{schedule} s{splits}", flush=True)
+    m = gqa(heads, kv, d)
+    run([(m, n) for n in [1, 15, 17, 32, 33, 64, 150, 700]], page_tokens, schedule, splits)
+
+
+def test_any_group_long_pieces():
+    """Unsplit pieces of more than 64 and 128 pages, both head widths in one launch."""
+    run([(gqa(28, 4), 2100), (gqa(16, 8, 64), 4300), (gqa(8, 1), 2081), (gqa(12, 12, 64), 2115)], 32, QUE, 1)
+
+
+@pytest.mark.parametrize("g", [4, 5])
+def test_split_probabilities_keep_fp32_precision(g):
+    """Probabilities are multiplied as the sum of two bf16 numbers. With V
+    equal to a constant (a power of two) in every row the output is that
+    constant times (sum of the operands) / (sum of the fp32 probabilities):
+    each operand pair is within 2^-17 of its probability, so the result
+    rounds to the constant exactly, and an infinite V stays infinite."""
+    hq = 4 * g
+    m, n = gqa(hq, 4), 1000
+    rng = np.random.default_rng(1)
+    rows = rng.standard_normal((n, m.row_width), dtype=np.float32)
+    rows[:, 4 * 128:] = 0.5
+    rows[:, 4 * 128 + 7] = np.inf
+    bits = (rows.view(np.uint32) >> 16).astype(np.uint16)
+    pool = cpl.Pool(page_tokens=64, pool_bytes=64 << 20, device=0)
+    rid = pool.open(pool.register_spec(m), n)
+    pool.append([rid], [n], to_device_u16(bits, "cuda"))
+    q = to_device_u16((rng.standard_normal((hq, 128), dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16), "cuda")
+    out = torch.zeros(hq * 128, dtype=torch.int16, device="cuda")
+    lse = torch.zeros(hq, dtype=torch.float32, device="cuda")
+    pool.decode([rid], q, out, lse)
+    torch.cuda.synchronize()
+    got = out.view(torch.bfloat16).float().cpu().numpy().reshape(hq, 128)
+    expect = np.full((hq, 128), 0.5, dtype=np.float32)
+    expect[:g, 7] = np.inf  # the heads of KV head 0
+    assert np.array_equal(got, expect)
+    pool.close(rid)
+    pool.destroy()
