@@ -785,16 +785,31 @@ void choose_valu(const Geom &g, GeomK *k, int32_t P) {
 
 constexpr int32_t kMatrixFirst = 16;  // variants from here on run on the matrix cores
 
-// Stream variant of a GQA / MHA model without a matrix variant of its own,
-// or -1. Slices of 16 (head_dim 128) or 32 (head_dim 64) tokens must tile
-// the pages. The automatic path takes it for groups of 1 to 4 heads: with 4
-// heads per KV head and 16 requests of 512 to 32K tokens a call moves 5.7
-// TB/s (80 us) where the small-group vector kernel moved 3.8 (122 us), and
-// with groups of 1 to 3 and head_dim 64 in one batch 5.0 against 2.0.
-int32_t stream_variant(const Geom &g, int32_t P) {
-  if (g.kind != kGQA || g.g > 4) return -1;
-  if (g.head_dim == 128 && P % 16 == 0) return kT_D128;
-  if (g.head_dim == 64 && P % 32 == 0) return kT_D64;
+// Matrix-core variant that keeps P to 2^-17 (two bf16 operands) for a model
+// without a matrix variant of its own, or -1; *nb: units per KV head and KV
+// range. The automatic path takes one wherever the geometry and page size fit:
+//   GQA / MHA, head_dim 64 or 128 (slices of 32 or 16 tokens must tile the
+//     pages): with 4 heads per KV head and 16 requests of 512 to 32K tokens a
+//     call moves 5.7 TB/s (80 us) where the small-group vector kernel moved
+//     3.8 (122 us), with groups of 1 to 3 and head_dim 64 in one batch 5.0
+//     against 2.0; from 5 heads up the alternative is the generic vector
+//     kernel (0.1 to 0.3 TB/s).
+//   MLA with 512 + 64 wide rows: head pairs over 32-token tiles above 16
+//     heads, units of 16 heads over 16-token slices below and on smaller
+//     pages; again against the generic vector kernel.
+int32_t precise_variant(const Geom &g, int32_t P, int32_t *nb) {
+  if (g.kind == kGQA && (g.head_dim == 128 ? P % 16 == 0 : g.head_dim == 64 && P % 32 == 0)) {
+    *nb = (g.g + 15) / 16;
+    return g.head_dim == 128 ? kT_D128 : kT_D64;
+  }
+  if (g.kind == kMLA && g.latent == 512 && g.rope == 64 && P % 16 == 0) {
+    if (g.g > 16 && P % 32 == 0) {
+      *nb = (g.g + 63) / 64;
+      return g.g <= 32 ? kM_MLA_H32 : kM_MLA_H64;
+    }
+    *nb = (g.g + 15) / 16;
+    return kM_MLA_G16S;
+  }
   return -1;
 }
 
@@ -808,7 +823,7 @@ int32_t stream_variant(const Geom &g, int32_t P) {
 int32_t matrix_variant(const Geom &g, int32_t P) {
   if (g.kind == kMLA && g.latent == 512 && g.rope == 64) {
     if (g.g == 16 && P % 16 == 0) return kM_MLA_G16;
-    if (g.g == 32 && P % 16 == 0) return kM_MLA_G32;
+    if (g.g == 32 && P % 16 == 0) return P % 32 == 0 ? kM_MLA_H32 : kM_MLA_G16;  // (two units of 16)
     if (g.g == 128 && P % 32 == 0) return kM_MLA_G128;
     return -1;
   }
@@ -912,10 +927,10 @@ cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const vo
     const int32_t mv = o.path == CP_PATH_VALU ? -1 : matrix_variant(g, P);
     if (mv >= 0) {
       gk[m].variant = mv;
-      gk[m].nb = mv == kM_MLA_G32 ? 2 : 1;  // units of 16 heads per KV range
-    } else if (const int32_t sv = o.path == CP_PATH_AUTO ? stream_variant(g, P) : -1; sv >= 0) {
-      gk[m].variant = sv;
-      gk[m].nb = (g.g + 15) / 16;  // units of up to 16 heads per KV head
+      gk[m].nb = mv == kM_MLA_G16 ? g.g / 16 : 1;  // units of 16 heads per KV range
+    } else if (int32_t nb = 1, pv = o.path == CP_PATH_AUTO ? precise_variant(g, P, &nb) : -1; pv >= 0) {
+      gk[m].variant = pv;
+      gk[m].nb = nb;
     } else {
       choose_valu(g, &gk[m], P);
     }
@@ -990,19 +1005,12 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
     pages[i] = (pl->attend[i] + P - 1) / P;
   }
   if (qo > 0xFFFFFFFFull || oo > 0xFFFFFFFFull) return fail(CP_EINVAL, "batch too large");
-  // kernel family: vector variants share a launch, narrow matrix variants
-  // share another, head-owner and stream ones a launch each, and 128-head
-  // MLA has a kernel of its own
+  // kernel family: generic vector variants share a launch, small-group vector
+  // ones another, and the eight-wave matrix variants a third; 128-head MLA
+  // has a kernel of its own
   auto wclass = [&](int32_t i) {
     const int v = gk[model_of(i)].variant;
-    // (launch classes: vector, narrow matrix, small-group vector, head-owner
-    // matrix, stream matrix, 128-head MLA)
-    return is_mla_wide(v)                               ? v
-           : is_many_heads(v)                           ? 3
-           : is_stream(v)                               ? 4
-           : v >= kMatrixFirst                          ? 1
-           : (v >= kS_G1_D64 && v <= kS_G4_D128)        ? 2
-                                                        : 0;
+    return is_mla_wide(v) ? v : v >= kMatrixFirst ? 1 : (v >= kS_G1_D64 && v <= kS_G4_D128) ? 2 : 0;
   };
 
   // Launch groups: requests whose kernels share a workgroup size, at most

@@ -61,7 +61,7 @@ __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm,
                                            char *lds) {
   using C = HeadsCfg<G, D>;
   constexpr int T = C::T;
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_ids().lane;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int stream = wave / C::HW, hw = wave % C::HW;
   const int col = lane & 15, quad = lane >> 4;

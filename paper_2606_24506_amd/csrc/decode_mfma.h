@@ -116,4 +116,19 @@ CP_DEV float xor_sum_16_32(float x) {
   return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
+// Lane index and its mfma coordinates, counted afresh by the lane-count
+// instructions at every use: the compiler can neither hoist them nor keep
+// the thread index alive across the loop for them. A unit that takes its
+// lane from here also keeps the compiler from hoisting its per-lane values
+// out of the work loop, where those of every variant of a kernel would be
+// live together.
+struct LaneIds {
+  int lane, col, quad;
+};
+CP_DEV LaneIds lane_ids() {
+  int t;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(t));
+  return LaneIds{t, t & 15, t >> 4};
+}
+
 }  // namespace cp

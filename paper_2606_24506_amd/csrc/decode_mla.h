@@ -87,18 +87,6 @@ struct MlaCfg {
 CP_DEV int mla_vswz(int r) { return (2 * r) & 15; }
 CP_DEV int mla_rswz(int r) { return r & 6; }
 
-// Lane index and its mfma coordinates, counted afresh by the lane-count
-// instructions at every use: the compiler can neither hoist them nor keep
-// the thread index alive across the loop for them.
-struct LaneIds {
-  int lane, col, quad;
-};
-CP_DEV LaneIds lane_ids() {
-  int t;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(t));
-  return LaneIds{t, t & 15, t >> 4};
-}
-
 // V^T operand fragment of value column block b of a tile slot: this lane
 // supplies value rows vr and vr + 16, bytes 8 (col & 3) of the block.
 CP_DEV bf16x8 mla_vfrag(const char *vslot, const LaneIds &L, int b) {

@@ -1,5 +1,5 @@
-// Matrix-core decode path for 8 to 32 query heads per KV head (MLA-16/32
-// on one latent head; MQA and GQA groups with head_dim 128). Per KV byte
+// Matrix-core decode path for 8 to 32 query heads per KV head (MLA-16, or
+// any MLA head count in units of 16, on one latent head; MQA and GQA groups with head_dim 128). Per KV byte
 // there are only 8-32 flops here, so the kernel is built to hide memory and
 // LDS latency rather than to feed the matrix cores: a workgroup of NW = 8
 // waves (two per SIMD, so one wave's stalls are the other's issue slots)
@@ -32,7 +32,7 @@
 namespace cp {
 
 // G: query heads one unit handles (a model group of 8 is padded to 16; an
-// MLA group of 32 runs as two units of 16, since 32 heads x 512 columns of
+// MLA group above 16 runs as units of 16, since 32 heads x 512 columns of
 // accumulators would not leave registers for the rest).
 template <int G, int DK, int DV, bool MLA, int TW, int NW, int SHARE, int NSLOT>
 struct NarrowCfg {
@@ -69,11 +69,20 @@ struct NarrowCfg {
   static_assert(LDS <= 163840, "LDS budget");
 };
 
-template <int G, int DK, int DV, bool MLA, int TW, int NW, int SHARE, int NSLOT>
+// PS: bf16 operands that P.V takes P as, 1 (p rounded) or 2 (cut and rest, at
+// most 2^-17 of p left out, for head counts whose other kernel is the fp32
+// vector one; the rest is kept above zero so that an infinite V stays
+// infinite). FRESH: the lane index is counted afresh, which keeps a kernel of
+// many variants from holding the per-lane values of all of them through its
+// work loop (64 registers spilled against 25); the kernels of one to three
+// variants fit without, and then form those values once per launch instead of
+// once per piece (mixed MLA-16 / MQA-32 / GQA-8 step: 147 us, with FRESH 161).
+template <int G, int DK, int DV, bool MLA, int TW, int NW, int SHARE, int NSLOT, int PS, bool FRESH>
 __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm, const DecReq &rq, const Seg &sg,
                                             char *lds) {
   using C = NarrowCfg<G, DK, DV, MLA, TW, NW, SHARE, NSLOT>;
-  const int lane = threadIdx.x & 63;
+  static_assert(PS == 1 || (PS == 2 && TW == 16), "two operands with 16-token slices");
+  const int lane = FRESH ? lane_ids().lane : threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int stream = wave % C::NSTREAM, member = wave / C::NSTREAM;
   const int col = lane & 15, quad = lane >> 4;
@@ -336,7 +345,7 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
     }
     // ---- P (fp32 into the row sums, bf16 as the P.V operand) and O^T += V^T P^T
     if constexpr (TW == 16) {
-      s16x4 pf[C::HBW];
+      s16x4 pf[C::HBW], pr[C::HBW];
 #pragma unroll
       for (int hb = 0; hb < C::HBW; ++hb) {
         float ps = 0.f;
@@ -344,7 +353,13 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
         for (int r = 0; r < 4; ++r) {
           const float p = fast_exp2(__builtin_fmaf(sv[0][hb][r], sl2, -m[hb]));
           ps += p;
-          pf[hb][r] = __builtin_bit_cast(short, (__bf16)p);
+          if constexpr (PS == 1) {
+            pf[hb][r] = __builtin_bit_cast(short, (__bf16)p);
+          } else {
+            const uint32_t cut = __float_as_uint(p) & 0xFFFF0000u;
+            pf[hb][r] = (short)(cut >> 16);
+            pr[hb][r] = __builtin_bit_cast(short, (__bf16)__builtin_fmaxf(p - __uint_as_float(cut), 1e-37f));
+          }
         }
         lsum[hb] += ps;
       }
@@ -371,6 +386,14 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
           for (int hb = 0; hb < C::HBW; ++hb)
             o[hb][b * C::VB + j] =
                 __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[b & 1][j], pf[hb], o[hb][b * C::VB + j], 0, 0, 0);
+        if constexpr (PS == 2) {
+#pragma unroll
+          for (int j = 0; j < C::VB; ++j)
+#pragma unroll
+            for (int hb = 0; hb < C::HBW; ++hb)
+              o[hb][b * C::VB + j] =
+                  __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[b & 1][j], pr[hb], o[hb][b * C::VB + j], 0, 0, 0);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {

@@ -75,7 +75,7 @@ __device__ __forceinline__ void stream_unit(const DecodeArgs &a, const GeomK &gm
                                             char *lds) {
   using C = StreamCfg<D>;
   constexpr int TW = C::TW;
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_ids().lane;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4;
   const int P = gm.page_tokens;  // the host routes only pages of a multiple of TW tokens here

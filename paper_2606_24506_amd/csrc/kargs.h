@@ -38,17 +38,21 @@ constexpr uint32_t kPieceFixedCost = 40;
 //     1, 2 or 4 query heads per KV head and head_dim 64 or 128 (the forced
 //     vector path, and pages the stream path does not tile).
 //   Narrow matrix path (16, 17, 19, 20, 23): 8, 16 or 32 query heads per KV
-//     head (MLA latent head, or head_dim 128).
+//     head (MLA latent head, or head_dim 128); 17 is MLA in units of up to
+//     16 heads with P as two bf16 operands.
 //   Head-owner matrix path (21, 22): 64 or 128 query heads per KV head with
 //     head_dim 128.
 //   Stream matrix path (24, 25): any other GQA / MHA group, head_dim 64 or
 //     128, in units of up to 16 heads; P as two bf16 operands.
+//   MLA head-pair path (26, 27): MLA with 17 to 32 heads, or in units of up
+//     to 64; P as two bf16 operands.
 //   128-head MLA (18): its own kernel (score waves and P.V waves).
 enum : int32_t {
   kV16x8 = 0, kV16x4, kV16x2, kV16x1, kV8x8, kV8x4, kV8x2, kV8x1,
   kS_G1_D64 = 8, kS_G2_D64, kS_G4_D64, kS_G1_D128, kS_G2_D128, kS_G4_D128,
-  kM_MLA_G16 = 16, kM_MLA_G32, kM_MLA_G128, kM_D128_G16, kM_D128_G32, kM_D128_G64, kM_D128_G128, kM_D128_G8,
-  kT_D64 = 24, kT_D128
+  kM_MLA_G16 = 16, kM_MLA_G16S, kM_MLA_G128, kM_D128_G16, kM_D128_G32, kM_D128_G64, kM_D128_G128, kM_D128_G8,
+  kT_D64 = 24, kT_D128,
+  kM_MLA_H32 = 26, kM_MLA_H64
 };
 constexpr bool is_stream(int v) { return v == kT_D64 || v == kT_D128; }
 constexpr bool is_mla_wide(int v) { return v == kM_MLA_G128; }

@@ -15,6 +15,7 @@
 
 #include "decode_heads.h"
 #include "decode_mfma.h"
+#include "decode_mla_heads.h"
 #include "decode_narrow.h"
 #include "decode_small.h"
 #include "decode_stream.h"
@@ -278,11 +279,11 @@ __device__ __forceinline__ void valu_unit(const DecodeArgs &a, const GeomK &gm, 
 // per stream, ring slots per stream).
 constexpr int kNarrowWaves = 8;
 template <int V> struct NarrowVar;
-template <> struct NarrowVar<kM_MLA_G16> { static constexpr int G = 16, DK = 576, DV = 512, TW = 16, SHARE = 2, NSLOT = 2; static constexpr bool MLA = true; };
-template <> struct NarrowVar<kM_MLA_G32> { static constexpr int G = 16, DK = 576, DV = 512, TW = 16, SHARE = 2, NSLOT = 2; static constexpr bool MLA = true; };
-template <> struct NarrowVar<kM_D128_G8> { static constexpr int G = 8, DK = 128, DV = 128, TW = 32, SHARE = 2, NSLOT = 2; static constexpr bool MLA = false; };
-template <> struct NarrowVar<kM_D128_G16> { static constexpr int G = 16, DK = 128, DV = 128, TW = 32, SHARE = 2, NSLOT = 2; static constexpr bool MLA = false; };
-template <> struct NarrowVar<kM_D128_G32> { static constexpr int G = 32, DK = 128, DV = 128, TW = 32, SHARE = 2, NSLOT = 2; static constexpr bool MLA = false; };
+template <> struct NarrowVar<kM_MLA_G16> { static constexpr int G = 16, DK = 576, DV = 512, TW = 16, SHARE = 2, NSLOT = 2, PS = 1; static constexpr bool MLA = true; };
+template <> struct NarrowVar<kM_MLA_G16S> { static constexpr int G = 16, DK = 576, DV = 512, TW = 16, SHARE = 2, NSLOT = 2, PS = 2; static constexpr bool MLA = true; };
+template <> struct NarrowVar<kM_D128_G8> { static constexpr int G = 8, DK = 128, DV = 128, TW = 32, SHARE = 2, NSLOT = 2, PS = 1; static constexpr bool MLA = false; };
+template <> struct NarrowVar<kM_D128_G16> { static constexpr int G = 16, DK = 128, DV = 128, TW = 32, SHARE = 2, NSLOT = 2, PS = 1; static constexpr bool MLA = false; };
+template <> struct NarrowVar<kM_D128_G32> { static constexpr int G = 32, DK = 128, DV = 128, TW = 32, SHARE = 2, NSLOT = 2, PS = 1; static constexpr bool MLA = false; };
 template <int V>
 using NarrowCfgOf = NarrowCfg<NarrowVar<V>::G, NarrowVar<V>::DK, NarrowVar<V>::DV, NarrowVar<V>::MLA, NarrowVar<V>::TW,
                               kNarrowWaves, NarrowVar<V>::SHARE, NarrowVar<V>::NSLOT>;
@@ -300,6 +301,7 @@ constexpr int narrow_lds() { return NarrowCfgOf<V>::LDS; }
 constexpr bool has(uint32_t mask, int v) { return (mask >> v) & 1u; }
 constexpr uint32_t kValuMask = 0xFFu;
 constexpr uint32_t kSmallMask = 0x3F00u;  // variants 8-13
+constexpr uint32_t kManyMask = 3u << kM_MLA_H32;  // of the kernels with narrow variants, set only where every one is
 
 template <int V> struct SmallVar;
 template <> struct SmallVar<kS_G1_D64> { static constexpr int G = 1, D = 64; };
@@ -319,11 +321,13 @@ constexpr int kernel_lds_bytes(uint32_t mask) {
   CP_S(kS_G1_D64) CP_S(kS_G2_D64) CP_S(kS_G4_D64) CP_S(kS_G1_D128) CP_S(kS_G2_D128) CP_S(kS_G4_D128)
 #undef CP_S
 #define CP_B(V) if (has(mask, V) && narrow_lds<V>() > b) b = narrow_lds<V>();
-  CP_B(kM_MLA_G16) CP_B(kM_MLA_G32) CP_B(kM_D128_G8) CP_B(kM_D128_G16) CP_B(kM_D128_G32)
+  CP_B(kM_MLA_G16) CP_B(kM_MLA_G16S) CP_B(kM_D128_G8) CP_B(kM_D128_G16) CP_B(kM_D128_G32)
 #undef CP_B
 #define CP_H(V) if (has(mask, V) && HeadsCfgOf<V>::LDS > b) b = HeadsCfgOf<V>::LDS;
   CP_H(kM_D128_G64) CP_H(kM_D128_G128)
 #undef CP_H
+  if (has(mask, kM_MLA_H32) && MlaHeadsCfg<2>::LDS > b) b = MlaHeadsCfg<2>::LDS;
+  if (has(mask, kM_MLA_H64) && MlaHeadsCfg<4>::LDS > b) b = MlaHeadsCfg<4>::LDS;
   if (has(mask, kT_D64) && StreamCfg<64>::LDS > b) b = StreamCfg<64>::LDS;
   if (has(mask, kT_D128) && StreamCfg<128>::LDS > b) b = StreamCfg<128>::LDS;
   return b;
@@ -356,11 +360,11 @@ __device__ __forceinline__ void run_seg(const DecodeArgs &a, const DecReq &rq, c
   if constexpr (has(MASK, V)) {                                                              \
     if (gm.variant == V) {                                                                   \
       using W = NarrowVar<V>;                                                                \
-      narrow_unit<W::G, W::DK, W::DV, W::MLA, W::TW, kNarrowWaves, W::SHARE, W::NSLOT>(a, gm, rq, sg, lds); \
+      narrow_unit<W::G, W::DK, W::DV, W::MLA, W::TW, kNarrowWaves, W::SHARE, W::NSLOT, W::PS, (MASK & kManyMask) != 0>(a, gm, rq, sg, lds); \
       return;                                                                                \
     }                                                                                        \
   }
-  CP_NCASE(kM_MLA_G16) CP_NCASE(kM_MLA_G32) CP_NCASE(kM_D128_G8) CP_NCASE(kM_D128_G16) CP_NCASE(kM_D128_G32)
+  CP_NCASE(kM_MLA_G16) CP_NCASE(kM_MLA_G16S) CP_NCASE(kM_D128_G8) CP_NCASE(kM_D128_G16) CP_NCASE(kM_D128_G32)
 #undef CP_NCASE
 #define CP_HCASE(V)                                                      \
   if constexpr (has(MASK, V)) {                                          \
@@ -371,6 +375,18 @@ __device__ __forceinline__ void run_seg(const DecodeArgs &a, const DecReq &rq, c
   }
   CP_HCASE(kM_D128_G64) CP_HCASE(kM_D128_G128)
 #undef CP_HCASE
+  if constexpr (has(MASK, kM_MLA_H32)) {
+    if (gm.variant == kM_MLA_H32) {
+      mla_heads_unit<2>(a, gm, rq, sg, lds);
+      return;
+    }
+  }
+  if constexpr (has(MASK, kM_MLA_H64)) {
+    if (gm.variant == kM_MLA_H64) {
+      mla_heads_unit<4>(a, gm, rq, sg, lds);
+      return;
+    }
+  }
   if constexpr (has(MASK, kT_D64)) {
     if (gm.variant == kT_D64) {
       stream_unit<64>(a, gm, rq, sg, lds);
@@ -402,12 +418,15 @@ __global__ __launch_bounds__(64 * kernel_waves<MASK>()) void decode_kernel(const
 }
 
 constexpr uint32_t vbit(int v) { return 1u << v; }
-// The variant sets the host launches together: each single variant, and
-// the mixed MLA-16 / MQA-32 / GQA-8 batch.
+// The variant sets the host launches together: each single variant, the
+// mixed MLA-16 / MQA-32 / GQA-8 batch, the head-owner, stream and MLA
+// head-pair variants, and every matrix variant.
 constexpr uint32_t kMixedSmall = vbit(kM_MLA_G16) | vbit(kM_D128_G32) | vbit(kM_D128_G8);
 constexpr uint32_t kAllHeads = vbit(kM_D128_G64) | vbit(kM_D128_G128);
-constexpr uint32_t kAllNarrow =
-    vbit(kM_MLA_G16) | vbit(kM_MLA_G32) | vbit(kM_D128_G16) | vbit(kM_D128_G32) | vbit(kM_D128_G8);
+constexpr uint32_t kAllStream = vbit(kT_D64) | vbit(kT_D128);
+constexpr uint32_t kAllMlaHeads = vbit(kM_MLA_H32) | vbit(kM_MLA_H64);
+constexpr uint32_t kAllMatrix = vbit(kM_MLA_G16) | vbit(kM_MLA_G16S) | vbit(kM_D128_G16) | vbit(kM_D128_G32) |
+                                vbit(kM_D128_G8) | kAllHeads | kAllStream | kAllMlaHeads;
 
 // Picks the kernel instantiation that covers `mask`. Returns
 // hipErrorInvalidValue for a set no instantiation covers (the host keeps
@@ -423,11 +442,12 @@ hipError_t launch_decode(const DecodeArgs &a, int grid, uint32_t mask, hipStream
   switch (mask) {
     CP_L(vbit(kV16x8)) CP_L(vbit(kV16x4)) CP_L(vbit(kV16x2)) CP_L(vbit(kV16x1))
     CP_L(vbit(kV8x8)) CP_L(vbit(kV8x4)) CP_L(vbit(kV8x2)) CP_L(vbit(kV8x1))
-    CP_L(vbit(kM_MLA_G16)) CP_L(vbit(kM_MLA_G32)) CP_L(vbit(kM_D128_G16)) CP_L(vbit(kM_D128_G32))
+    CP_L(vbit(kM_MLA_G16)) CP_L(vbit(kM_MLA_G16S)) CP_L(vbit(kM_D128_G16)) CP_L(vbit(kM_D128_G32))
     CP_L(vbit(kM_D128_G8))
     CP_L(kMixedSmall)
     CP_L(vbit(kM_D128_G64)) CP_L(vbit(kM_D128_G128)) CP_L(kAllHeads)
-    CP_L(vbit(kT_D64)) CP_L(vbit(kT_D128)) CP_L(vbit(kT_D64) | vbit(kT_D128))
+    CP_L(vbit(kT_D64)) CP_L(vbit(kT_D128)) CP_L(kAllStream)
+    CP_L(vbit(kM_MLA_H32)) CP_L(vbit(kM_MLA_H64)) CP_L(kAllMlaHeads)
     CP_L(vbit(kS_G1_D64)) CP_L(vbit(kS_G2_D64)) CP_L(vbit(kS_G4_D64)) CP_L(vbit(kS_G1_D128)) CP_L(vbit(kS_G2_D128))
     CP_L(vbit(kS_G4_D128))
     default: break;
@@ -441,8 +461,13 @@ hipError_t launch_decode(const DecodeArgs &a, int grid, uint32_t mask, hipStream
     hipExtLaunchKernelGGL((decode_kernel<kSmallMask>), g, dim3(256), 0, stream, ev0, ev1, 0, a);
     return hipGetLastError();
   }
-  if ((mask & ~kAllNarrow) == 0) {
-    hipExtLaunchKernelGGL((decode_kernel<kAllNarrow>), g, dim3(64 * kNarrowWaves), 0, stream, ev0, ev1, 0, a);
+  constexpr uint32_t kWide = kAllHeads | kAllStream | kAllMlaHeads;
+  if ((mask & ~kWide) == 0) {
+    hipExtLaunchKernelGGL((decode_kernel<kWide>), g, dim3(64 * kNarrowWaves), 0, stream, ev0, ev1, 0, a);
+    return hipGetLastError();
+  }
+  if ((mask & ~kAllMatrix) == 0) {
+    hipExtLaunchKernelGGL((decode_kernel<kAllMatrix>), g, dim3(64 * kNarrowWaves), 0, stream, ev0, ev1, 0, a);
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
@@ -453,7 +478,7 @@ hipError_t launch_decode(const DecodeArgs &a, int grid, uint32_t mask, hipStream
 int matrix_streams(int variant) {
   switch (variant) {
     case kM_MLA_G16: return NarrowCfgOf<kM_MLA_G16>::NSTREAM;
-    case kM_MLA_G32: return NarrowCfgOf<kM_MLA_G32>::NSTREAM;
+    case kM_MLA_G16S: return NarrowCfgOf<kM_MLA_G16S>::NSTREAM;
     case kM_D128_G8: return NarrowCfgOf<kM_D128_G8>::NSTREAM;
     case kM_D128_G16: return NarrowCfgOf<kM_D128_G16>::NSTREAM;
     case kM_D128_G32: return NarrowCfgOf<kM_D128_G32>::NSTREAM;
@@ -471,11 +496,13 @@ int decode_wgs_per_cu(uint32_t mask) {
   int b = 16;
   if (mask & 0xFFu) b = kLdsFloats * 4;
 #define CP_B(V) if (has(mask, V) && narrow_lds<V>() > b) b = narrow_lds<V>();
-  CP_B(kM_MLA_G16) CP_B(kM_MLA_G32) CP_B(kM_D128_G8) CP_B(kM_D128_G16) CP_B(kM_D128_G32)
+  CP_B(kM_MLA_G16) CP_B(kM_MLA_G16S) CP_B(kM_D128_G8) CP_B(kM_D128_G16) CP_B(kM_D128_G32)
 #undef CP_B
 #define CP_H(V) if (has(mask, V) && HeadsCfgOf<V>::LDS > b) b = HeadsCfgOf<V>::LDS;
   CP_H(kM_D128_G64) CP_H(kM_D128_G128)
 #undef CP_H
+  if (has(mask, kM_MLA_H32) && MlaHeadsCfg<2>::LDS > b) b = MlaHeadsCfg<2>::LDS;
+  if (has(mask, kM_MLA_H64) && MlaHeadsCfg<4>::LDS > b) b = MlaHeadsCfg<4>::LDS;
   if (has(mask, kT_D64) && StreamCfg<64>::LDS > b) b = StreamCfg<64>::LDS;
   if (has(mask, kT_D128) && StreamCfg<128>::LDS > b) b = StreamCfg<128>::LDS;
   const int per = (160 * 1024) / (b + 64);

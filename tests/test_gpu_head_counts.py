@@ -25,6 +25,10 @@ def gqa(heads, kv, d=128):
     return ModelSpec(f"gqa{heads}x{kv}d{d}", "gqa", heads, kv, head_dim=d, scale=1 / math.sqrt(d))
 
 
+def mla(heads):
+    return ModelSpec(f"mla{heads}", "mla", heads, 1, latent_dim=512, rope_dim=64, scale=1 / math.sqrt(192.0))
+
+
 def run(specs_lens, page_tokens, schedule, splits, kind="staircase", seed=3):
     """Decodes one request per (spec, length) and compares each with the
     oracle, at the bars of every parity test here."""
@@ -99,6 +103,25 @@ def test_any_group(heads, kv, d, page_tokens, schedule, splits):
 def test_any_group_long_pieces():
     """Unsplit pieces of more than 64 and 128 pages, both head widths in one launch."""
     run([(gqa(28, 4), 2100), (gqa(16, 8, 64), 4300), (gqa(8, 1), 2081), (gqa(12, 12, 64), 2115)], 32, QUE, 1)
+
+
+# MLA: one unit of 16 (padded), head pairs in two streams (to 32) or one (to
+# 64), several units of 64; pages of 16 and 48 tokens take units of 16
+@pytest.mark.parametrize("heads", [6, 15, 17, 20, 32, 33, 64, 100, 144])
+@pytest.mark.parametrize("page_tokens,schedule,splits", [(64, BAL, 0), (32, QUE, 1), (48, QUE, 3)])
+def test_any_mla_head_count(heads, page_tokens, schedule, splits):
+    print(f"[case] MLA-{heads} P{page_tokens} sched{schedule} s{splits}", flush=True)
+    run([(mla(heads), n) for n in [1, 15, 17, 32, 33, 64, 95, 500]], page_tokens, schedule, splits)
+
+
+def test_any_mla_head_count_long_pieces():
+    """Unsplit pieces of more than 64 and 128 pages, variants sharing a launch."""
+    run([(mla(20), 2100), (mla(64), 4300), (mla(7), 2081), (mla(32), 2115)], 32, QUE, 1)
+
+
+def test_mla_128_on_small_pages():
+    """128 heads on pages that 32-token tiles do not fit: units of 16 heads."""
+    run([(mla(128), n) for n in (1, 17, 300)], 16, BAL, 0)
 
 
 @pytest.mark.parametrize("g", [4, 5])
