@@ -158,30 +158,47 @@ struct MergeArgs {
   MergeReq req[kMaxReqPerLaunch];
 };
 
+// Append and gather: a workgroup of kCopyThreads copies up to kCopyUnroll
+// 16-byte segments per thread, and so this many rows (a power of two where the
+// page allows it, so that a workgroup seldom meets two pages).
+constexpr int kCopyThreads = 256, kCopyUnroll = 5;
+constexpr uint32_t copy_rows_per_block(uint32_t row_elems, uint32_t page_tokens) {
+  const uint32_t fit = (uint32_t)(kCopyThreads * kCopyUnroll) / (row_elems / 8);
+  uint32_t r = 1;
+  while (2 * r <= fit) r *= 2;
+  return r < page_tokens ? r : page_tokens;
+}
+
 struct AppReq {
-  uint64_t src_off;    // bf16 element offset of the request's first row in the input
-  uint32_t row_begin;  // first grid row of this request in the launch
+  uint64_t src_off;      // bf16 element offset of the request's first row in the input
+  uint32_t block_begin;  // first workgroup of this request in the launch
   uint32_t n_new;
   uint32_t old_len;
   uint32_t pte_base;
-  uint32_t model;
+  uint16_t model;
+  uint16_t ent;  // index in AppendArgs::ent of its first new page's entry (kNoEnt: in the page table)
   uint32_t pad;
 };
+constexpr uint16_t kNoEnt = 0xFFFFu;
+// New page-table entries one append launch carries; appends that open more
+// pages copy theirs to the device first.
+constexpr int kAppEntMax = 352;
 
 struct AppendArgs {
   uint8_t *pool;
-  const uint32_t *pte;
+  uint32_t *pte;  // written only where a new page's entry comes with the launch
   const uint16_t *rows;
-  int32_t n_req, total_rows, pad0, pad1;
+  int32_t n_req, n_blocks, n_ent, pad1;
   GeomK geom[kMaxLaunchModels];
   AppReq req[kMaxReqPerLaunch];
+  uint32_t ent[kAppEntMax];
 };
 
 struct GatherArgs {
   const uint8_t *pool;
   const uint32_t *pte;
   uint16_t *dst;
-  uint32_t pte_base, start, n_tok, pad;
+  uint32_t pte_base, plane, start, n_tok;  // plane: page-table entries from one KV plane to the next
   GeomK geom;
 };
 
@@ -201,6 +218,6 @@ static_assert(sizeof(StackPushArgs) <= 3072, "stack push arguments too large");
 // the argument segment (with the runtime's hidden arguments) stays under 4 KiB
 static_assert(sizeof(DecodeArgs) <= 3776, "decode kernel arguments too large");
 static_assert(sizeof(MergeArgs) <= 3072, "merge kernel arguments too large");
-static_assert(sizeof(AppendArgs) <= 3072, "append kernel arguments too large");
+static_assert(sizeof(AppendArgs) <= 3776, "append kernel arguments too large");
 
 }  // namespace cp
