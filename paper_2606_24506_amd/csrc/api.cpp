@@ -27,6 +27,7 @@ hipError_t launch_decode_mla(const DecodeArgs &a, int grid, int variant, hipStre
                               hipEvent_t ev1);
 int decode_wgs_per_cu(uint32_t mask);
 int matrix_streams(int variant);
+int matrix_step_tokens(int variant, int hkv);
 hipError_t launch_merge(const MergeArgs &a, hipStream_t stream);
 hipError_t launch_stack_push(const StackPushArgs &a, hipStream_t stream);
 hipError_t scratch_device_address(int device, void **out);
@@ -950,10 +951,17 @@ cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const vo
     } else {
       choose_valu(g, &gk[m], P);
     }
-    // relative work of one page: its bytes, times the head blocks that each
-    // reread it on the MLA vector path and on the stream path
-    const int64_t unit = std::max<int64_t>(1, (g.page_bytes + 8191) / 8192);
-    gk[m].page_cost = (int32_t)(unit * (g.kind == kMLA || is_stream(gk[m].variant) ? gk[m].nb : 1));
+    // a block: a page, or for pages of more than 128 KiB what the kernel
+    // works through in one step (six requests of groups of 1 to 4 heads,
+    // 128-1024 tokens, 64-token pages of 128 and 256 KiB: 14.4 us a call against
+    // 19.4 with whole pages; cutting 32 to 128 KiB pages too gained nothing and
+    // cost 1 to 4% on batches that small, by more partials). Its relative
+    // work: its bytes, times the head blocks that each reread it on the MLA
+    // vector path and on the stream path.
+    const int32_t step = matrix_step_tokens(gk[m].variant, g.hkv);
+    gk[m].blk_tokens = g.page_bytes > (128 << 10) && step > 0 && P % step == 0 ? step : P;
+    const int64_t kib = ((int64_t)gk[m].blk_tokens * g.kappa + 1023) / 1024;
+    gk[m].blk_cost = (int32_t)(kib * (g.kind == kMLA || is_stream(gk[m].variant) ? gk[m].nb : 1));
   }
   for (int32_t i = 0; i < n; ++i) {
     const int32_t m = p->st.req(req_ids[i]).model;
@@ -964,6 +972,10 @@ cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const vo
   *gk_out = std::move(gk);
   return CP_OK;
 }
+
+// The balanced schedule's ranges hold no less than this (one MLA page of 64
+// tokens), or a page of models with smaller ones.
+constexpr uint64_t kMinRangeKib = 72;
 
 // Everything one decode call launches: per-request offsets, launch groups,
 // split plan and workspace layout. Built and checked in full before any
@@ -1008,7 +1020,7 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
   pl->q_off.assign(n, 0);
   pl->o_off.assign(n, 0);
   pl->l_off.assign(n, 0);
-  std::vector<int64_t> pages(n);
+  std::vector<int64_t> blocks(n);  // balanced schedule: blocks of GeomK::blk_tokens tokens
   uint64_t qo = 0, oo = 0, lo = 0;
   for (int32_t i = 0; i < n; ++i) {
     const Geom &g = p->st.model(model_of(i));
@@ -1018,7 +1030,6 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
     qo += (uint64_t)g.hq * g.d_k;
     oo += (uint64_t)g.hq * g.d_v;
     lo += (uint64_t)g.hq;
-    pages[i] = (pl->attend[i] + P - 1) / P;
   }
   if (qo > 0xFFFFFFFFull || oo > 0xFFFFFFFFull) return fail(CP_EINVAL, "batch too large");
   // kernel family: generic vector variants share a launch, small-group vector
@@ -1076,30 +1087,36 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
       // (equal requests over a multiple of their count of workgroups).
       uint64_t T0 = 0, maxc = 1;
       for (int32_t i : g.idx) {
-        const uint64_t c = (uint64_t)gk[model_of(i)].page_cost;
-        T0 += (uint64_t)pages[i] * c;
-        maxc = std::max(maxc, c);
+        const GeomK &k = gk[model_of(i)];
+        const uint64_t c = (uint64_t)k.blk_cost;
+        blocks[i] = (pl->attend[i] + k.blk_tokens - 1) / k.blk_tokens;
+        T0 += (uint64_t)blocks[i] * c;
+        // a range spans at least a block of every model, and a page of those
+        // whose pages are smaller than kMinRangeKib (splitting further makes
+        // more partials without shortening the launch)
+        const uint64_t page = c * (uint64_t)(P / k.blk_tokens);
+        maxc = std::max({maxc, c, std::min<uint64_t>(page, kMinRangeKib)});
       }
       const uint64_t W0 = std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)slots, T0 / maxc));
       uint64_t T = 0, pre0 = 0;
       for (size_t k = 0; k < g.idx.size(); ++k) {
         const int32_t i = g.idx[k];
-        const uint64_t c = (uint64_t)gk[model_of(i)].page_cost;
+        const uint64_t c = (uint64_t)gk[model_of(i)].blk_cost;
         const bool straddled = k > 0 && (pre0 * W0) % T0 != 0;
         T += straddled ? kPieceFixedCost : 0;
-        cost_prefix[i] = (uint32_t)std::min<uint64_t>(T, 0xFFFFFFFFull);  // the request's first page
-        T += (uint64_t)pages[i] * c;
-        pre0 += (uint64_t)pages[i] * c;
+        cost_prefix[i] = (uint32_t)std::min<uint64_t>(T, 0xFFFFFFFFull);  // the request's first block
+        T += (uint64_t)blocks[i] * c;
+        pre0 += (uint64_t)blocks[i] * c;
       }
       if (T > 0xFFFFFFFFull) return fail(CP_EINVAL, "batch too large for one launch");
-      // every range spans at least one page of any model, so no request has
+      // every range spans at least one block of any model, so no request has
       // an empty slot between its first and last worker
       const uint64_t W = std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)slots, T / maxc));
       auto owner = [&](uint64_t x) { return (uint32_t)(((x + 1) * W - 1) / T); };
       for (int32_t i : g.idx) {
-        // page j of the request sits at C + j c
-        const uint64_t c = (uint64_t)gk[model_of(i)].page_cost, C = cost_prefix[i];
-        const uint32_t w0 = owner(C), w1 = owner(C + (uint64_t)(pages[i] - 1) * c);
+        // block j of the request sits at C + j c
+        const uint64_t c = (uint64_t)gk[model_of(i)].blk_cost, C = cost_prefix[i];
+        const uint32_t w0 = owner(C), w1 = owner(C + (uint64_t)(blocks[i] - 1) * c);
         first_worker[i] = (int32_t)w0;
         n_slots[i] = (int32_t)(w1 - w0 + 1);
       }

@@ -54,7 +54,7 @@ struct HeadsCfg {
   static_assert(NSLOT >= 3 && LDS <= 163840 - 64, "ring depth and LDS budget");
 };
 
-// One unit: pages [sg.pg_begin, sg.pg_end) of a request for KV head sg.hblk
+// One unit: tokens [sg.tok_begin, sg.tok_end) of a request for KV head sg.hblk
 // (or NSTREAM consecutive KV heads, one per stream).
 template <int G, int D>
 __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm, const DecReq &rq, const Seg &sg,
@@ -72,22 +72,23 @@ __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm,
   const int kvh = head_par ? C::NSTREAM * (int)sg.hblk + stream : (int)sg.hblk;
   const int h0 = kvh * G + 16 * hw;  // first query head of this wave
 
-  const uint32_t tok_begin = sg.pg_begin * (uint32_t)P;
-  const uint32_t tok_end = min(rq.ctx_len, sg.pg_end * (uint32_t)P);
+  const uint32_t tok_begin = sg.tok_begin, tok_end = sg.tok_end;
+  const uint32_t pg0 = tok_begin / (uint32_t)P;  // the piece may start inside a page:
+  const int off = (int)(tok_begin - pg0 * (uint32_t)P) / T;  // ... by this many tiles
   const int ntiles = (int)((tok_end - tok_begin + T - 1) / T);
   const int first = head_par ? 0 : stream, step = head_par ? 1 : C::NSTREAM;  // this stream's tiles
   const int mine = ntiles > first ? (ntiles - first + step - 1) / step : 0;
   const int iters = head_par ? ntiles : (ntiles + C::NSTREAM - 1) / C::NSTREAM;  // the same in every wave
   const uint64_t kv_head_bytes = (uint64_t)2 * P * C::ROW;
   char *const ring = lds + stream * (C::NSLOT * C::TILE);
-  const int npg = (int)((tok_end + P - 1) / P) - (int)sg.pg_begin;
+  const int npg = (int)((tok_end + P - 1) / P) - (int)pg0;
 
   // page-table entries of the unit, 64 at a time (lane i: page 64 b + i)
   uint32_t pte_lane = 0;
   int pte_batch = -1;
   auto load_ptes = [&](int batch) {
     const int sp = batch * 64 + lane;
-    pte_lane = sp < npg ? a.pte[rq.pte_base + sg.pg_begin + (uint32_t)sp] : 0u;
+    pte_lane = sp < npg ? a.pte[rq.pte_base + pg0 + (uint32_t)sp] : 0u;
     pte_batch = batch;
     // a visible wait: the tile loads are inline asm the compiler cannot
     // count, so its own wait at the first use would drain them every tile
@@ -103,7 +104,7 @@ __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm,
               1024u * (j & 3);
   }
   auto issue = [&](int i) {
-    const int tl = first + step * i, sp = tl / tpp;  // tile and page within the unit
+    const int tl = off + first + step * i, sp = tl / tpp;  // tile, from the unit's first page on, and page
     if ((sp >> 6) != pte_batch) load_ptes(sp >> 6);
     const uint32_t pte = __builtin_amdgcn_readlane(pte_lane, sp & 63);
     const uint64_t sb = uniform_ptr(a.pool + ((uint64_t)pte << 8) + (uint64_t)kvh * kv_head_bytes +

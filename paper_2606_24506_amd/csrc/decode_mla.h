@@ -123,8 +123,8 @@ __device__ __forceinline__ void mla_unit(const DecodeArgs &a, const GeomK &gm, c
   char *const pbuf = lds + C::OFF_P;
   char *const xbuf = lds + C::OFF_X;
 
-  const uint32_t tok_end = min(rq.ctx_len, sg.pg_end * (uint32_t)P);
-  const uint32_t pg_begin = sg.pg_begin;
+  const uint32_t tok_end = sg.tok_end;
+  const uint32_t pg_begin = sg.tok_begin / (uint32_t)P;  // pieces of this kernel are whole pages
   const int npg = (int)((tok_end + P - 1) / P) - (int)pg_begin;
   const int last_tok = npg > 0 ? (int)tok_end - (int)((pg_begin + (uint32_t)npg - 1) * (uint32_t)P) : 0;
   const int ntiles = npg > 0 ? (npg - 1) * tpp + (last_tok + T - 1) / T : 0;

@@ -77,13 +77,14 @@ __device__ __forceinline__ void mla_heads_unit(const DecodeArgs &a, const GeomK 
   const int hv = min(16, gm.g - h0);                 // its valid heads (none or fewer when padded)
   const int nb0 = member * C::NBW;                   // first value column block of this wave
 
-  const uint32_t tok_begin = sg.pg_begin * (uint32_t)P;
-  const uint32_t tok_end = min(rq.ctx_len, sg.pg_end * (uint32_t)P);
+  const uint32_t tok_begin = sg.tok_begin, tok_end = sg.tok_end;
+  const uint32_t pg0 = tok_begin / (uint32_t)P;  // the piece may start inside a page:
+  const int off = (int)(tok_begin - pg0 * (uint32_t)P) / T;  // ... by this many tiles
   const int ntok = (int)(tok_end - tok_begin);
   const int ntiles = (ntok + T - 1) / T;
   const int mine = ntiles > stream ? (ntiles - stream + C::NSTREAM - 1) / C::NSTREAM : 0;
   const int iters = (ntiles + C::NSTREAM - 1) / C::NSTREAM;  // the same in every wave
-  const int npg = (ntok + P - 1) / P;
+  const int npg = (int)((tok_end + P - 1) / P) - (int)pg0;
   char *const ring = lds + stream * (C::NSLOT * C::TILE);
 
   // page-table entries of the unit, 64 at a time (lane i: page 64 b + i)
@@ -91,7 +92,7 @@ __device__ __forceinline__ void mla_heads_unit(const DecodeArgs &a, const GeomK 
   int pte_batch = -1;
   auto load_ptes = [&](int batch) {
     const int sp = batch * 64 + lane;
-    pte_lane = sp < npg ? a.pte[rq.pte_base + sg.pg_begin + (uint32_t)sp] : 0u;
+    pte_lane = sp < npg ? a.pte[rq.pte_base + pg0 + (uint32_t)sp] : 0u;
     pte_batch = batch;
     // a visible wait: the tile loads are inline asm the compiler cannot
     // count, so its own wait at the first use would drain them every tile
@@ -100,7 +101,7 @@ __device__ __forceinline__ void mla_heads_unit(const DecodeArgs &a, const GeomK 
   // This wave loads value rows VLW wis .. + VLW - 1 of a tile (a KiB each) and
   // as many rotary rows (one load; half its lanes when VLW = 4).
   auto issue = [&](int i) {
-    const int tl = stream + C::NSTREAM * i, sp = tl / tpp;
+    const int tl = off + stream + C::NSTREAM * i, sp = tl / tpp;  // tile, from the unit's first page on, and page
     if ((sp >> 6) != pte_batch) load_ptes(sp >> 6);
     const uint32_t pte = __builtin_amdgcn_readlane(pte_lane, sp & 63);
     const uint64_t sb = uniform_ptr(a.pool + ((uint64_t)pte << 8) + (uint64_t)(tl % tpp) * T * C::KROW - kDmaBias);

@@ -100,8 +100,9 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
   const int hv = min(C::HEADS, gm.g - sub * C::HEADS);  // valid heads (fewer when padded)
   const int nb0 = member * C::NBLKW;                     // first V column block of this wave
 
-  const uint32_t tok_begin = sg.pg_begin * (uint32_t)P;
-  const uint32_t tok_end = min(rq.ctx_len, sg.pg_end * (uint32_t)P);
+  const uint32_t tok_begin = sg.tok_begin, tok_end = sg.tok_end;
+  const uint32_t pg0 = tok_begin / (uint32_t)P;  // the piece may start inside a page:
+  const int off = (int)(tok_begin - pg0 * (uint32_t)P) / TW;  // ... by this many slices
   const int nslices = (int)((tok_end - tok_begin + TW - 1) / TW);
   const int first = head_par ? 0 : stream;      // this stream's first slice
   const int step = head_par ? 1 : C::NSTREAM;   // ... and the stride between its slices
@@ -111,14 +112,14 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
   const int iters = SHARE == 1 ? mine : (head_par ? nslices : (nslices + C::NSTREAM - 1) / C::NSTREAM);
   const uint64_t kv_head_bytes = MLA ? 0 : (uint64_t)2 * P * DK * 2;
   char *const ring = lds + stream * (NSLOT * C::SLICE);
-  const int npg = (int)((tok_end + P - 1) / P) - (int)sg.pg_begin;
+  const int npg = (int)((tok_end + P - 1) / P) - (int)pg0;
 
   // Page-table entries of the unit, 64 at a time (lane i: page 64 b + i).
   uint32_t pte_lane = 0;
   int pte_batch = -1;
   auto load_ptes = [&](int batch) {
     const int sp = batch * 64 + lane;
-    pte_lane = sp < npg ? a.pte[rq.pte_base + sg.pg_begin + (uint32_t)sp] : 0u;
+    pte_lane = sp < npg ? a.pte[rq.pte_base + pg0 + (uint32_t)sp] : 0u;
     pte_batch = batch;
     // visible to the compiler, which cannot count the inline-asm slice
     // loads: otherwise it would drain them before every use of pte_lane
@@ -150,8 +151,8 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
     }
   // Issues this member's loads of the stream's i-th slice into slot i % NSLOT.
   auto issue = [&](int i) {
-    const int sl = first + step * i;  // slice within the unit
-    const int sp = sl / spp;          // page within the unit
+    const int sl = off + first + step * i;  // slice, from the unit's first page on
+    const int sp = sl / spp;                // page within the unit
     if ((sp >> 6) != pte_batch) load_ptes(sp >> 6);
     const uint32_t pte = __builtin_amdgcn_readlane(pte_lane, sp & 63);
     const uint64_t sb = uniform_ptr(a.pool + ((uint64_t)pte << 8) + (uint64_t)kvh * kv_head_bytes +

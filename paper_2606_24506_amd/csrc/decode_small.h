@@ -98,11 +98,11 @@ __device__ __forceinline__ void small_unit(const DecodeArgs &a, const GeomK &gm,
     unpack8(u, q[h]);
   }
 
-  const uint32_t tok_begin = sg.pg_begin * (uint32_t)P;
-  const uint32_t tok_end = min(rq.ctx_len, sg.pg_end * (uint32_t)P);
+  const uint32_t tok_begin = sg.tok_begin, tok_end = sg.tok_end;  // whole pages
+  const uint32_t pg0 = tok_begin / (uint32_t)P;
   const int nsteps = (int)((tok_end - tok_begin + C::SUB - 1) / C::SUB);
   const uint64_t head_blk = (uint64_t)2 * P * D * 2;
-  const int npg = (int)((tok_end + P - 1) / P) - (int)sg.pg_begin;
+  const int npg = (int)((tok_end + P - 1) / P) - (int)pg0;
 
   // page-table entries of the range, 64 at a time (lane i: page 64 b + i)
   uint32_t pte_lane = 0;
@@ -110,11 +110,11 @@ __device__ __forceinline__ void small_unit(const DecodeArgs &a, const GeomK &gm,
   // Loads of step j: K and V rows of tokens tok_begin + 16 j + TPI i + r.
   auto load_step = [&](int j, u32x4n (&kb)[C::NI], u32x4n (&vb)[C::NI]) __attribute__((always_inline)) {
     const uint32_t t0 = tok_begin + (uint32_t)(C::SUB * j);
-    const int sp = (int)(t0 / (uint32_t)P) - (int)sg.pg_begin;  // page within the range
+    const int sp = (int)(t0 / (uint32_t)P) - (int)pg0;  // page within the range
     if ((sp >> 6) != pte_batch) {
       pte_batch = sp >> 6;
       const int pi = 64 * pte_batch + lane;
-      pte_lane = pi < npg ? a.pte[rq.pte_base + sg.pg_begin + (uint32_t)pi] : 0u;
+      pte_lane = pi < npg ? a.pte[rq.pte_base + pg0 + (uint32_t)pi] : 0u;
     }
     const uint32_t pte = __builtin_amdgcn_readlane(pte_lane, sp & 63);
     const uint8_t *kp = a.pool + ((uint64_t)pte << 8) + (uint64_t)kvh * head_blk +

@@ -63,7 +63,7 @@ struct StreamCfg {
 };
 
 // KV heads a workgroup takes side by side.
-CP_DEV int stream_heads(int hkv) {
+__host__ __device__ constexpr int stream_heads(int hkv) {
   const int low = hkv & -hkv;
   return low < 8 ? low : 8;
 }
@@ -87,12 +87,13 @@ __device__ __forceinline__ void stream_unit(const DecodeArgs &a, const GeomK &gm
   const int h0 = kvh * gm.g + sub * C::HEADS;           // first query head of this wave
   const int hv = min(C::HEADS, gm.g - sub * C::HEADS);  // ... and how many it has
 
-  const uint32_t tok_begin = sg.pg_begin * (uint32_t)P;
-  const uint32_t tok_end = min(rq.ctx_len, sg.pg_end * (uint32_t)P);
+  const uint32_t tok_begin = sg.tok_begin, tok_end = sg.tok_end;
+  const uint32_t pg0 = tok_begin / (uint32_t)P;  // the piece may start inside a page:
+  const int off = (int)(tok_begin - pg0 * (uint32_t)P) / TW;  // ... by this many slices
   const int ntok = (int)(tok_end - tok_begin);
   const int nslices = (ntok + TW - 1) / TW;
   const int mine = nslices > ts ? (nslices - ts + NT - 1) / NT : 0;
-  const int npg = (ntok + P - 1) / P;
+  const int npg = (int)((tok_end + P - 1) / P) - (int)pg0;
   char *const ring = lds + wave * (C::NSLOT * C::SLICE);
 
   // page-table entries of the unit, 64 at a time (lane i: page 64 b + i)
@@ -100,7 +101,7 @@ __device__ __forceinline__ void stream_unit(const DecodeArgs &a, const GeomK &gm
   int pte_batch = -1;
   auto load_ptes = [&](int batch) {
     const int sp = batch * 64 + lane;
-    pte_lane = sp < npg ? a.pte[rq.pte_base + sg.pg_begin + (uint32_t)sp] : 0u;
+    pte_lane = sp < npg ? a.pte[rq.pte_base + pg0 + (uint32_t)sp] : 0u;
     pte_batch = batch;
     // a visible wait: the slice loads are inline asm the compiler cannot
     // count, so its own wait at the first use would drain them every slice
@@ -114,7 +115,7 @@ __device__ __forceinline__ void stream_unit(const DecodeArgs &a, const GeomK &gm
     voff[j] = (uint32_t)(row * C::ROW + 16 * ((lane % C::CPR) ^ sw)) + kDmaBias - 1024u * j;
   }
   auto issue = [&](int i) {
-    const int sl = ts + NT * i, sp = sl / spp;  // slice and page within the unit
+    const int sl = off + ts + NT * i, sp = sl / spp;  // slice, from the unit's first page on, and page
     if ((sp >> 6) != pte_batch) load_ptes(sp >> 6);
     const uint32_t pte = __builtin_amdgcn_readlane(pte_lane, sp & 63);
     const uint64_t sb = uniform_ptr(a.pool + ((uint64_t)pte << 8) + (uint64_t)kvh * (2u * (uint32_t)P * C::ROW) +

@@ -20,16 +20,18 @@ constexpr int32_t kStackCap = 8192;
 // most) when a step needs more than it holds.
 constexpr int32_t kStackRefill = 1024;
 enum : int32_t { kSchedBalanced = 0, kSchedQueue = 1, kSchedGrid = 2 };
-// Balanced schedule: the fixed work of one piece (page-table and query
-// loads, the latency of its first pages under a loaded memory system, the
-// end merge and the partial write), in page-cost units (8 KiB of page
-// bytes each): measured at about 23K cycles per piece on the narrow kernel,
-// which streams about 600 cycles per unit. A request boundary that falls
-// inside a workgroup's share is preceded by that much cost on the cost
-// line, so the workgroup that runs a second piece there takes
-// correspondingly fewer pages. DecReq::unit_begin is the cost position of
-// the request's first page.
-constexpr uint32_t kPieceFixedCost = 40;
+// Balanced schedule. The cost line counts KiB of KV; a request's stretch of it
+// is cut between blocks of GeomK::blk_tokens tokens: pages, or for large pages
+// the tokens that the model's kernel works through in one step of its loop.
+// The fixed work of one piece (page-table and query loads, the latency of its
+// first pages under a loaded memory system, the end merge and the partial
+// write) is charged as this many KiB: measured at about 23K cycles per piece
+// on the narrow kernel, which streams about 600 cycles per 8 KiB. A request
+// boundary that falls inside a workgroup's share is preceded by that much cost
+// on the cost line, so the workgroup that runs a second piece there takes
+// correspondingly less KV. DecReq::unit_begin is the cost position of the
+// request's first block.
+constexpr uint32_t kPieceFixedCost = 320;
 
 // Decode code paths (GeomK::variant), chosen per model by the host.
 //   Vector path (0-7): wavefront reductions; heads per block (16 or 8) and
@@ -59,11 +61,12 @@ constexpr bool is_mla_wide(int v) { return v == kM_MLA_G128; }
 // Variants with 64 or more heads per KV head, whose partials are large.
 constexpr bool is_many_heads(int v) { return v == kM_MLA_G128 || v == kM_D128_G64 || v == kM_D128_G128; }
 
-// One piece of decode work: pages [pg_begin, pg_end) of a request, for one
+// One piece of decode work: tokens [tok_begin, tok_end) of a request (whole
+// blocks, but for the last one of the context), for one
 // head block, writing partial slot `slot` when the request is split; model
 // is the request's index into DecodeArgs::geom.
 struct Seg {
-  uint32_t pg_begin, pg_end, slot, hblk, model;
+  uint32_t tok_begin, tok_end, slot, hblk, model;
 };
 
 // Per-model geometry as the kernels see it.
@@ -75,7 +78,8 @@ struct GeomK {
   int32_t variant;     // kernel code path chosen by the host
   float scale_log2;    // softmax scale * log2(e)
   int32_t nb;          // head blocks per KV head (vector path)
-  int32_t page_cost;   // relative work of one page (balanced schedule)
+  int32_t blk_tokens;  // balanced schedule: tokens of one block (divides page_tokens)
+  int32_t blk_cost;    // ... and its relative work
   int32_t pool_model;  // the model's id in the pool (its device page stack)
   int32_t layers;      // KV planes of a request of this model
 };
@@ -89,7 +93,7 @@ struct DecReq {
   uint32_t lse_off;   // float offset of its log-sum-exp values
   uint32_t ws_base;   // first partial lse row (kNoWs when the request is not split)
   uint32_t ws_orow;   // partial outputs start at element offset ws_orow * d_v
-  uint32_t unit_begin;   // queue/grid: first unit; balanced: cost position of the request's first page
+  uint32_t unit_begin;   // queue/grid: first unit; balanced: cost position of the request's first block
   uint16_t chunk_pages;  // queue/grid: pages per KV range; balanced: first worker of the request
   uint16_t n_chunks;     // KV ranges = partial slots
   uint8_t model;         // index into DecodeArgs::geom

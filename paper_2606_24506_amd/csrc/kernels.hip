@@ -194,8 +194,8 @@ __device__ __forceinline__ void valu_unit(const DecodeArgs &a, const GeomK &gm, 
   }
   __syncthreads();
 
-  const uint32_t tok_end = min(rq.ctx_len, sg.pg_end * (uint32_t)P);
-  const uint32_t pg_begin = sg.pg_begin;
+  const uint32_t tok_end = sg.tok_end;
+  const uint32_t pg_begin = sg.tok_begin / (uint32_t)P;  // whole pages
   const uint32_t pg_end = (tok_end + P - 1) / P;
   const uint64_t head_blk = gm.kind == 0 ? 0 : (uint64_t)2 * P * dk * 2;
   const uint32_t stride = (uint32_t)dk * 2;
@@ -525,6 +525,26 @@ hipError_t launch_decode(const DecodeArgs &a, int grid, uint32_t mask, hipStream
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
+}
+
+// Tokens a matrix variant's workgroup works through in one step of its loop
+// for a model of hkv KV heads, or 0 (vector variants and 128-head MLA, whose
+// pieces are whole pages).
+int matrix_step_tokens(int variant, int hkv) {
+  switch (variant) {
+    case kM_MLA_G16:
+    case kM_MLA_G16S: return 16 * NarrowCfgOf<kM_MLA_G16>::NSTREAM;
+    case kM_D128_G8:
+    case kM_D128_G16:
+    case kM_D128_G32: return hkv % NarrowCfgOf<kM_D128_G32>::NSTREAM == 0 ? 32 : 32 * NarrowCfgOf<kM_D128_G32>::NSTREAM;
+    case kM_D128_G64: return hkv % HeadsCfgOf<kM_D128_G64>::NSTREAM == 0 ? 32 : 32 * HeadsCfgOf<kM_D128_G64>::NSTREAM;
+    case kM_D128_G128: return 32;
+    case kT_D64: return StreamCfg<64>::TW * 8 / stream_heads(hkv);
+    case kT_D128: return StreamCfg<128>::TW * 8 / stream_heads(hkv);
+    case kM_MLA_H32: return 32 * MlaHeadsCfg<2>::NSTREAM;
+    case kM_MLA_H64: return 32 * MlaHeadsCfg<4>::NSTREAM;
+    default: return 0;
+  }
 }
 
 // Token streams of the workgroup for a matrix variant (KV heads a unit

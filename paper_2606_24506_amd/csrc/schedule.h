@@ -1,6 +1,6 @@
 // Work distribution shared by the decode kernels. A decode launch covers
 // several requests (possibly of different models); `seg(rq, sg)` runs one
-// piece of work: pages [sg.pg_begin, sg.pg_end) of request rq for KV head
+// piece of work: tokens [sg.tok_begin, sg.tok_end) of request rq for KV head
 // (or head block) sg.hblk, writing partial slot sg.slot when the request is
 // split.
 #pragma once
@@ -14,10 +14,10 @@ namespace cp {
 
 // Finds the next piece of work of this workgroup for the balanced
 // schedule: head block *hb or a later one of request *r, or the first head
-// block of a later request, whose pages meet the workgroup's share
-// [L0, L1) of the cost line (page j of a request sits at its cost position
-// plus j times its model's page cost). Lane i evaluates request i: one
-// round of loads from the argument segment (the models' page sizes and
+// block of a later request, whose blocks meet the workgroup's share
+// [L0, L1) of the cost line (block j of a request sits at its cost position
+// plus j times its model's block cost). Lane i evaluates request i: one
+// round of loads from the argument segment (the models' block sizes and
 // costs are uniform loads) and one ballot, so that the first piece of a
 // launch starts after a single round trip. All arithmetic fits 32 bits:
 // the host keeps the cost line below 2^32 and the grid below 2^16.
@@ -29,16 +29,16 @@ __device__ __forceinline__ bool next_balanced(const DecodeArgs &a, int *r, uint3
   const int i = threadIdx.x & 63;
   const DecReq &ri = a.req[i < a.n_req ? i : 0];
   const uint32_t C = ri.unit_begin, model = ri.model, nh = ri.n_hblk;
-  uint32_t P = (uint32_t)a.geom[0].page_tokens, c = (uint32_t)a.geom[0].page_cost;
+  uint32_t B = (uint32_t)a.geom[0].blk_tokens, c = (uint32_t)a.geom[0].blk_cost;
 #pragma unroll
   for (int m = 1; m < kMaxLaunchModels; ++m)
     if (model == (uint32_t)m) {
-      P = (uint32_t)a.geom[m].page_tokens;
-      c = (uint32_t)a.geom[m].page_cost;
+      B = (uint32_t)a.geom[m].blk_tokens;
+      c = (uint32_t)a.geom[m].blk_cost;
     }
-  const uint32_t pages = (ri.ctx_len + P - 1) / P;
+  const uint32_t blocks = (ri.ctx_len + B - 1) / B;
   const uint32_t jb = L0 > C ? (L0 - C + c - 1) / c : 0u;
-  const uint32_t je = C < L1 ? min(pages, (L1 - C + c - 1) / c) : 0u;
+  const uint32_t je = C < L1 ? min(blocks, (L1 - C + c - 1) / c) : 0u;
   const bool ok = i < a.n_req && i >= *r && jb < je && (i > *r || *hb < nh);
   const uint64_t b = __builtin_amdgcn_ballot_w64(ok);
   if (b == 0) return false;
@@ -47,8 +47,8 @@ __device__ __forceinline__ bool next_balanced(const DecodeArgs &a, int *r, uint3
     *r = k;
     *hb = 0;
   }
-  sg->pg_begin = __builtin_amdgcn_readlane(jb, k);
-  sg->pg_end = __builtin_amdgcn_readlane(je, k);
+  sg->tok_begin = __builtin_amdgcn_readlane(jb * B, k);
+  sg->tok_end = __builtin_amdgcn_readlane(min(ri.ctx_len, je * B), k);
   sg->slot = w - __builtin_amdgcn_readlane((uint32_t)ri.chunk_pages, k);
   sg->hblk = *hb;
   sg->model = __builtin_amdgcn_readlane(model, k);
@@ -61,9 +61,9 @@ __device__ __forceinline__ int unit_segment(const DecodeArgs &a, uint32_t u, Seg
   const DecReq &rq = a.req[r];
   const uint32_t local = u - rq.unit_begin;
   const uint32_t chunk = local / rq.n_hblk;
-  const uint32_t pages = (rq.ctx_len + a.geom[rq.model].page_tokens - 1) / a.geom[rq.model].page_tokens;
-  sg->pg_begin = chunk * rq.chunk_pages;
-  sg->pg_end = min(pages, sg->pg_begin + rq.chunk_pages);
+  const uint32_t toks = (uint32_t)rq.chunk_pages * (uint32_t)a.geom[rq.model].page_tokens;
+  sg->tok_begin = chunk * toks;
+  sg->tok_end = min(rq.ctx_len, sg->tok_begin + toks);
   sg->slot = chunk;
   sg->hblk = local % rq.n_hblk;
   sg->model = rq.model;
@@ -99,7 +99,7 @@ __device__ __forceinline__ uint32_t pop_new_pages(const DecodeArgs &a, const Dec
   return __hip_atomic_load(a.pte + rq.pte_base + pg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Fused append (cp_attn_decode_step): every piece whose page range holds a
+// Fused append (cp_attn_decode_step): every piece whose tokens include a
 // request's last context token, when that token is new in this call, first
 // writes the page-table entry of a newly allocated page (taken from the
 // launch arguments, or popped from the model's device stack) and copies
@@ -111,7 +111,7 @@ __device__ __forceinline__ void fused_append(const DecodeArgs &a, const DecReq &
   const GeomK &g = a.geom[sg.model];
   const uint32_t P = (uint32_t)g.page_tokens;
   const uint32_t pos = rq.ctx_len - 1, pg = pos / P;
-  if (pg < sg.pg_begin || pg >= sg.pg_end) return;
+  if (pos < sg.tok_begin || pos >= sg.tok_end) return;
   uint32_t pte;
   if (rq.app_flags & kAppPop) {
     __shared__ uint32_t popped;

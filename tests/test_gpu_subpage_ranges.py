@@ -1,0 +1,64 @@
+"""Balanced schedules that cut ranges inside pages (models whose pages hold more
+than 128 KiB): every kernel family that serves such models, against the
+oracle, and decode steps whose fused append meets such ranges, bit for bit
+against append and decode."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_24506_amd import crosspool as cpl
+from test_gpu_head_counts import BAL, gqa, mla, run
+from workloads.harness import to_device_u16
+
+pytestmark = pytest.mark.gpu
+
+LENS = [1, 31, 33, 65, 130, 257, 700]
+
+
+@pytest.mark.parametrize("model,page_tokens", [
+    (gqa(32, 8), 64), (gqa(16, 16), 64), (gqa(30, 6), 128), (gqa(32, 16, 64), 128), (gqa(64, 8), 64),
+    (gqa(32, 1), 512), (gqa(128, 2), 256), (gqa(256, 2), 192), (mla(16), 128), (mla(12), 256), (mla(20), 128),
+    (mla(64), 128), (mla(32), 192)], ids=lambda x: getattr(x, "name", x))
+def test_ranges_inside_pages(model, page_tokens):
+    print(f"[case] {model.name} P{page_tokens}", flush=True)
+    run([(model, n) for n in LENS], page_tokens, BAL, 0)
+
+
+def test_models_of_different_blocks_in_one_launch():
+    run([(gqa(32, 8), 700), (mla(20), 300), (gqa(28, 4), 500), (mla(64), 129), (gqa(32, 8), 65)], 64, BAL, 0)
+
+
+@pytest.mark.parametrize("model,page_tokens", [(gqa(32, 8), 64), (gqa(64, 8), 64), (mla(16), 256), (mla(64), 128)],
+                         ids=lambda x: getattr(x, "name", x))
+def test_fused_step_over_ranges_inside_pages(model, page_tokens):
+    """Contexts around page ends and in the middle of a page; the step and
+    the two calls it stands for run on two pools holding the same rows."""
+    lens = [page_tokens - 1, page_tokens, 2 * page_tokens + page_tokens // 2 + 3, 5 * page_tokens - 2]
+    rng = np.random.default_rng(3)
+    rows = [rng.standard_normal((n + 3, model.row_width), dtype=np.float32) for n in lens]
+    bits = [(x.view(np.uint32) >> 16).astype(np.uint16) for x in rows]
+    q = rng.standard_normal((len(lens), model.n_q_heads, model.d_k), dtype=np.float32)
+    q = to_device_u16((q.view(np.uint32) >> 16).astype(np.uint16), "cuda")
+    pools = [cpl.Pool(page_tokens=page_tokens, pool_bytes=128 << 20, placement_seed=s, device=0) for s in (2, 9)]
+    res = [[], []]
+    for k, pool in enumerate(pools):
+        mid = pool.register_spec(model)
+        ids = [pool.open(mid, n + 3) for n in lens]
+        for r, n in zip(range(len(lens)), lens):
+            pool.append([ids[r]], [n], to_device_u16(bits[r][:n], "cuda"))
+        for t in range(3):
+            new = to_device_u16(np.concatenate([b[n + t] for b, n in zip(bits, lens)]), "cuda")
+            out = torch.zeros(len(lens) * model.n_q_heads * model.d_v, dtype=torch.int16, device="cuda")
+            lse = torch.zeros(len(lens) * model.n_q_heads, dtype=torch.float32, device="cuda")
+            if k == 0:
+                pool.decode_step(ids, [1] * len(lens), new, q, out, lse)
+            else:
+                pool.append(ids, [1] * len(lens), new)
+                pool.decode(ids, q, out, lse)
+            torch.cuda.synchronize()
+            res[k].append((out, lse))
+        for r in ids:
+            pool.close(r)
+        pool.destroy()
+    for (o0, l0), (o1, l1) in zip(*res):
+        assert torch.equal(o0, o1) and torch.equal(l0.view(torch.int32), l1.view(torch.int32))
