@@ -10,8 +10,8 @@
 // ordered {4q..4q+3, 16+4q..16+4q+3} for lane group q), and its softmax
 // state and its 16 x 128 outputs are its own. HW = G / 16 waves form a token
 // stream that shares a ring of NSLOT tiles of T = 32 tokens, filled by direct
-// non-temporal loads NSLOT - 1 tiles ahead; one barrier per tile frees a
-// slot. With fewer than 128 heads several streams run side by side: each
+// non-temporal loads NSLOT - 2 tiles ahead; one barrier per two tiles frees
+// their slots. With fewer than 128 heads several streams run side by side: each
 // takes KV heads of its own when the model's KV heads are a multiple of the
 // stream count, and interleaved tiles otherwise (their softmax states are
 // then merged through LDS at the end of the piece).
@@ -22,7 +22,8 @@
 // group) and the V transpose reads are then free of bank conflicts.
 //
 // Measured on 13 MQA-128 and 3 GQA-128:2 requests of 1K-64K tokens (183 MB of
-// KV): 45.7 us in one launch (4.0 TB/s), where a workgroup of four waves that
+// KV): 42.7 us in one launch (4.3 TB/s; 45.1 with a barrier and a softmax
+// update per tile), where a workgroup of four waves that
 // split scores by heads and P.V by columns, with P and the rescale factors
 // going through LDS and two barriers per tile, took 66.5 and 37.4 us in a
 // launch per group size (about 4,300 cycles per tile, 512 of them products).
@@ -51,7 +52,7 @@ struct HeadsCfg {
   static_assert(G == 64 || G == 128, "whole head blocks, one per wave");
   static_assert(D == 128, "rows of 16 chunks");
   static_assert(LPW == 2 || LPW % 4 == 0, "direct loads in groups");
-  static_assert(NSLOT >= 3 && LDS <= 163840 - 64, "ring depth and LDS budget");
+  static_assert(NSLOT >= 4 && NSLOT % 2 == 0 && LDS <= 163840 - 64, "ring depth and LDS budget");
 };
 
 // One unit: tokens [sg.tok_begin, sg.tok_end) of a request for KV head sg.hblk
@@ -78,7 +79,7 @@ __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm,
   const int ntiles = (int)((tok_end - tok_begin + T - 1) / T);
   const int first = head_par ? 0 : stream, step = head_par ? 1 : C::NSTREAM;  // this stream's tiles
   const int mine = ntiles > first ? (ntiles - first + step - 1) / step : 0;
-  const int iters = head_par ? ntiles : (ntiles + C::NSTREAM - 1) / C::NSTREAM;  // the same in every wave
+  const int most = head_par ? ntiles : (ntiles + C::NSTREAM - 1) / C::NSTREAM;  // tiles of any stream
   const uint64_t kv_head_bytes = (uint64_t)2 * P * C::ROW;
   char *const ring = lds + stream * (C::NSLOT * C::TILE);
   const int npg = (int)((tok_end + P - 1) / P) - (int)pg0;
@@ -136,7 +137,7 @@ __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm,
   const float sl2 = gm.scale_log2;
 
   load_ptes(0);  // its wait covers the query loads too
-  for (int i = 0; i < C::NSLOT - 1 && i < mine; ++i) issue(i);
+  for (int i = 0; i < C::NSLOT - 2 && i < mine; ++i) issue(i);
 
   // LDS byte offsets within a tile. K fragment of slice u, k-step c: row 16 u
   // + col, chunk 4 c + quad; V^T fragment of column block nb: rows 4 quad +
@@ -145,73 +146,87 @@ __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm,
   const int vr = 4 * quad + (col >> 2);
   const uint32_t vrow = (uint32_t)(T * C::ROW + vr * C::ROW + 8 * (col & 1)), vsw = (2 * vr) & 15;
 
+  // Two tiles (64 tokens) per iteration: one barrier, one softmax update, and
+  // twice the independent products and LDS reads to cover their latencies.
 #pragma unroll 1
-  for (int i = 0; i < iters; ++i) {
-    // own loads of tile i have landed once at most the later tiles' remain
-    const int later = mine - 1 - i;
-    if (later >= C::NSLOT - 2) wait_vm<C::LPW *(C::NSLOT - 2)>();
-    else if (C::NSLOT > 3 && later == 1) wait_vm<C::LPW>();
-    else if (C::NSLOT > 4 && later == 2) wait_vm<2 * C::LPW>();
-    else if (C::NSLOT > 5 && later == 3) wait_vm<3 * C::LPW>();
-    else if (C::NSLOT > 6 && later == 4) wait_vm<4 * C::LPW>();
-    else if (C::NSLOT > 7 && later == 5) wait_vm<5 * C::LPW>();
+  for (int i = 0; i < most; i += 2) {
+    // own loads of tiles i and i + 1 have landed once at most those of the
+    // later tiles issued so far (up to tile i + NSLOT - 3) remain
+    const int later = mine - 2 - i;
+    if (later >= C::NSLOT - 4) wait_vm<C::LPW *(C::NSLOT - 4)>();
+    else if (C::NSLOT > 5 && later == 1) wait_vm<C::LPW>();
+    else if (C::NSLOT > 6 && later == 2) wait_vm<2 * C::LPW>();
+    else if (C::NSLOT > 7 && later == 3) wait_vm<3 * C::LPW>();
     else wait_vm<0>();
-    __syncthreads();  // tile i is visible to the stream; the slot of tile i-1 is free
+    __syncthreads();  // both tiles are visible to the stream; the slots of tiles i-2 and i-1 are free
+    if (i + C::NSLOT - 2 < mine) issue(i + C::NSLOT - 2);
     if (i + C::NSLOT - 1 < mine) issue(i + C::NSLOT - 1);
     if (i >= mine) continue;
-    const char *tb = ring + (i % C::NSLOT) * C::TILE;
-    const int valid = min(T, (int)(tok_end - tok_begin) - (first + step * i) * T);
+    // tokens of the two tiles; the second is absent (negative) at an odd end
+    int valid[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) valid[k] = i + k < mine ? min(T, (int)(tok_end - tok_begin) - (first + step * (i + k)) * T) : 0;
 
-    // ---- scores of both 16-token slices; the V^T fragments are read behind
-    // the K fragments, so that they arrive during the softmax
-    bf16x8 kf[2][C::KSTEPS];
+    // ---- scores of the four 16-token slices; each tile's V^T fragments are
+    // read behind its K fragments, so that they arrive during the products
+    f32x4 s[4];
+    bf16x8 vf[2][C::NBLK];
 #pragma unroll
-    for (int c = 0; c < C::KSTEPS; ++c)
+    for (int k = 0; k < 2; ++k) {
+      const char *tb = ring + ((i + k) % C::NSLOT) * C::TILE;
+      bf16x8 kf[2][C::KSTEPS];
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-        kf[u][c] = *reinterpret_cast<const bf16x8 *>(tb + krow + u * 16 * C::ROW + 16 * ((4 * c + quad) ^ ksw));
-    bf16x8 vf[C::NBLK];
+      for (int c = 0; c < C::KSTEPS; ++c)
 #pragma unroll
-    for (int nb = 0; nb < C::NBLK; ++nb) {
-      const char *p0 = tb + vrow + 16 * ((2 * nb + ((col >> 1) & 1)) ^ vsw);
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p0);
-      const s16x4 hi =
-          __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p0 + 16 * C::ROW));
-      vf[nb] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    f32x4 s[2];
+        for (int u = 0; u < 2; ++u)
+          kf[u][c] = *reinterpret_cast<const bf16x8 *>(tb + krow + u * 16 * C::ROW + 16 * ((4 * c + quad) ^ ksw));
 #pragma unroll
-    for (int u = 0; u < 2; ++u) s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < C::KSTEPS; ++c)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) s[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[u][c], qf[c], s[u], 0, 0, 0);
-
-    // ---- online softmax (lane: head col, tokens 16 u + 4 quad + r). Scores
-    // stay unscaled: the positive scale goes onto the maximum and into the
-    // exponent's fma. The reference moves when some lane's own maximum
-    // passes it by kLazy; only then is the head's maximum taken across lanes.
-    if (valid < T) {
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (16 * u + 4 * quad + r >= valid) s[u][r] = -INFINITY;
-      // V rows past the context may hold stale bytes: their p is 0, and the
-      // operand's elements are zeroed so that 0 * V stays 0
-      u32x4h mask;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const int t = 16 * (w >> 1) + 4 * quad + 2 * (w & 1);
-        mask[w] = (t < valid ? 0xFFFFu : 0u) | (t + 1 < valid ? 0xFFFF0000u : 0u);
+      for (int nb = 0; nb < C::NBLK; ++nb) {
+        const char *p0 = tb + vrow + 16 * ((2 * nb + ((col >> 1) & 1)) ^ vsw);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p0);
+        const s16x4 hi =
+            __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p0 + 16 * C::ROW));
+        vf[k][nb] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
       }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int nb = 0; nb < C::NBLK; ++nb) vf[nb] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4h, vf[nb]) & mask);
+      for (int u = 0; u < 2; ++u) s[2 * k + u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < C::KSTEPS; ++c)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          s[2 * k + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[u][c], qf[c], s[2 * k + u], 0, 0, 0);
+    }
+
+    // ---- online softmax (lane: head col, tokens 16 u + 4 quad + r of a
+    // tile). Scores stay unscaled: the positive scale goes onto the maximum
+    // and into the exponent's fma. The reference moves when some lane's own
+    // maximum passes it by kLazy; only then is the head's maximum taken
+    // across lanes.
+    if (valid[0] + valid[1] < 2 * T) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (16 * u + 4 * quad + r >= valid[k]) s[2 * k + u][r] = -INFINITY;
+        // V rows past the context may hold stale bytes: their p is 0, and the
+        // operand's elements are zeroed so that 0 * V stays 0
+        u32x4h mask;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int t = 16 * (w >> 1) + 4 * quad + 2 * (w & 1);
+          mask[w] = (t < valid[k] ? 0xFFFFu : 0u) | (t + 1 < valid[k] ? 0xFFFF0000u : 0u);
+        }
+#pragma unroll
+        for (int nb = 0; nb < C::NBLK; ++nb)
+          vf[k][nb] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4h, vf[k][nb]) & mask);
+      }
     }
     float x = s[0][0];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r) x = __builtin_fmaxf(x, s[u][r]);
     if (__builtin_amdgcn_ballot_w64(x * sl2 > m + kLazy)) {
@@ -224,19 +239,23 @@ __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm,
       for (int nb = 0; nb < C::NBLK; ++nb) o[nb] *= al;
     }
     // ---- P (fp32 into the row sum, bf16 as the operand) and O^T += V^T P^T
-    bf16x8 pf;
     float ps = 0.f;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int k = 0; k < 2; ++k) {
+      bf16x8 pf;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float p = fast_exp2(__builtin_fmaf(s[u][r], sl2, -m));
-        ps += p;
-        pf[4 * u + r] = (__bf16)p;
-      }
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float p = fast_exp2(__builtin_fmaf(s[2 * k + u][r], sl2, -m));
+          ps += p;
+          pf[4 * u + r] = (__bf16)p;
+        }
+#pragma unroll
+      for (int nb = 0; nb < C::NBLK; ++nb)
+        o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[k][nb], pf, o[nb], 0, 0, 0);
+    }
     lsum += ps;
-#pragma unroll
-    for (int nb = 0; nb < C::NBLK; ++nb) o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[nb], pf, o[nb], 0, 0, 0);
   }
 
   // ---- unit end
