@@ -914,6 +914,26 @@ cp_status cp_attn_decode_ex(cp_pool *p, int32_t n, const int32_t *req_ids, const
 
 namespace {
 
+// Blocks of the balanced schedule's cost line. A block is a page, or for pages
+// of more than 128 KiB (unless `whole_pages`) what the kernel works through
+// in one step (six requests of groups of 1 to 4 heads, 128-1024 tokens,
+// 64-token pages of 128 and 256 KiB: 14.4 us a call against 19.4 with whole
+// pages; cutting 32 to 128 KiB pages too gained nothing and cost 1 to 4% on
+// batches that small, by more partials). Its relative work: its bytes, times
+// the head blocks that each reread it on the MLA vector path and on the
+// stream path.
+void set_blocks(cp_pool *p, std::vector<GeomK> *gk, bool whole_pages) {
+  const int32_t P = p->st.page_tokens();
+  for (int32_t m = 0; m < p->st.n_models(); ++m) {
+    const Geom &g = p->st.model(m);
+    GeomK &k = (*gk)[m];
+    const int32_t step = matrix_step_tokens(k.variant, g.hkv);
+    k.blk_tokens = !whole_pages && g.page_bytes > (128 << 10) && step > 0 && P % step == 0 ? step : P;
+    const int64_t kib = ((int64_t)k.blk_tokens * g.kappa + 1023) / 1024;
+    k.blk_cost = (int32_t)(kib * (g.kind == kMLA || is_stream(k.variant) ? k.nb : 1));
+  }
+}
+
 // Checks what every decode call needs; fills the options and the per-model
 // kernel geometry (variant, head blocking, page cost).
 cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const void *q, void *out, float *lse,
@@ -951,18 +971,8 @@ cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const vo
     } else {
       choose_valu(g, &gk[m], P);
     }
-    // a block: a page, or for pages of more than 128 KiB what the kernel
-    // works through in one step (six requests of groups of 1 to 4 heads,
-    // 128-1024 tokens, 64-token pages of 128 and 256 KiB: 14.4 us a call against
-    // 19.4 with whole pages; cutting 32 to 128 KiB pages too gained nothing and
-    // cost 1 to 4% on batches that small, by more partials). Its relative
-    // work: its bytes, times the head blocks that each reread it on the MLA
-    // vector path and on the stream path.
-    const int32_t step = matrix_step_tokens(gk[m].variant, g.hkv);
-    gk[m].blk_tokens = g.page_bytes > (128 << 10) && step > 0 && P % step == 0 ? step : P;
-    const int64_t kib = ((int64_t)gk[m].blk_tokens * g.kappa + 1023) / 1024;
-    gk[m].blk_cost = (int32_t)(kib * (g.kind == kMLA || is_stream(gk[m].variant) ? gk[m].nb : 1));
   }
+  set_blocks(p, &gk, false);
   for (int32_t i = 0; i < n; ++i) {
     const int32_t m = p->st.req(req_ids[i]).model;
     if (o.path == CP_PATH_MFMA && matrix_variant(p->st.model(m), P) < 0)
@@ -1509,11 +1519,18 @@ cp_status cp_attn_decode_noalloc(cp_pool *p, int32_t n, const int32_t *req_ids, 
   DecodePlan pl;
   cp_status rc = decode_prepare(p, n, req_ids, q, out, lse, opts, &pl.o, &pl.gk);
   if (rc) return rc;
-  rc = plan_decode(p, n, req_ids, nullptr, &pl);
-  if (rc) return rc;
-  // partial outputs first, then the partial lse values (256-byte aligned)
-  const uint64_t o_bytes = (pl.ws_elems * sizeof(uint16_t) + 255) / 256 * 256;
-  const uint64_t need = o_bytes + pl.ws_rows * sizeof(float);
+  // Partial outputs first, then the partial lse values (256-byte aligned).
+  // Ranges cut inside pages make more partials: a plan that outgrows the
+  // workspace with them is made again of whole pages.
+  uint64_t o_bytes = 0, need = 0;
+  for (int whole_pages = 0; whole_pages < 2; ++whole_pages) {
+    if (whole_pages) set_blocks(p, &pl.gk, true);
+    rc = plan_decode(p, n, req_ids, nullptr, &pl);
+    if (rc) return rc;
+    o_bytes = (pl.ws_elems * sizeof(uint16_t) + 255) / 256 * 256;
+    need = o_bytes + pl.ws_rows * sizeof(float);
+    if (need <= kNoAllocScratchBytes) break;
+  }
   if (need > kNoAllocScratchBytes)
     return fail(CP_EINVAL,
                 "the split plan needs %llu bytes of workspace; cp_attn_decode_noalloc has %llu (use fewer KV ranges: "
