@@ -986,6 +986,22 @@ cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const vo
 // The balanced schedule's ranges hold no less than this (one MLA page of 64
 // tokens), or a page of models with smaller ones.
 constexpr uint64_t kMinRangeKib = 72;
+constexpr int32_t kTimeWeightUnit = 8;
+
+// Time per KiB of KV, in eighths of what the narrow and stream kernels take:
+// the kernels of more heads per KV byte run below HBM speed, and where they
+// share a launch by bytes their workgroups end last. Swept on launches of
+// these models (24 requests of MLA-20, MLA-64, GQA-28:4 and GQA-40:8): 50.0 us a
+// call with 8 for each, 41.5 with 10 and 14, 38.5 with 12 and 18, 40.7 with 16 and 24;
+// MQA-128 with GQA-128:2: 48.2 with 8 and 8, 47.3 with 10 and 8, 52.2 with 8 and 12.
+int32_t time_weight(int32_t variant) {
+  switch (variant) {
+    case kM_MLA_H32: return 12;
+    case kM_MLA_H64: return 18;
+    case kM_D128_G128: return 10;
+    default: return kTimeWeightUnit;
+  }
+}
 
 // Everything one decode call launches: per-request offsets, launch groups,
 // split plan and workspace layout. Built and checked in full before any
@@ -998,8 +1014,10 @@ struct DecodePlan {
     int grid = 0;
     uint32_t total_cost = 0;
     uint32_t n_units = 0;
+    bool weighted = false;  // balanced: block costs times time_weight
   };
   cp_decode_opts o{};
+  bool whole_pages = false;  // ranges of whole pages, shared by bytes
   std::vector<GeomK> gk;
   std::vector<int64_t> attend;  // tokens each request attends over (call order)
   std::vector<uint64_t> q_off, o_off, l_off;
@@ -1095,25 +1113,44 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
       // not before the launch's first request, and not at a boundary that
       // coincides with a share boundary of the line without fixed costs
       // (equal requests over a multiple of their count of workgroups).
-      uint64_t T0 = 0, maxc = 1;
+      uint64_t T0 = 0, maxc = 1, T0w = 0, maxcw = 1;
+      int32_t wmin = 1 << 30, wmax = 0;
       for (int32_t i : g.idx) {
         const GeomK &k = gk[model_of(i)];
+        const int32_t w = time_weight(k.variant);
         const uint64_t c = (uint64_t)k.blk_cost;
         blocks[i] = (pl->attend[i] + k.blk_tokens - 1) / k.blk_tokens;
         T0 += (uint64_t)blocks[i] * c;
         // a range spans at least a block of every model, and a page of those
         // whose pages are smaller than kMinRangeKib (splitting further makes
         // more partials without shortening the launch)
-        const uint64_t page = c * (uint64_t)(P / k.blk_tokens);
-        maxc = std::max({maxc, c, std::min<uint64_t>(page, kMinRangeKib)});
+        const uint64_t page = c * (uint64_t)(P / k.blk_tokens), least = std::max(c, std::min<uint64_t>(page, kMinRangeKib));
+        maxc = std::max(maxc, least);
+        T0w += (uint64_t)blocks[i] * c * (uint64_t)w;
+        maxcw = std::max(maxcw, least * (uint64_t)w);
+        wmin = std::min(wmin, w);
+        wmax = std::max(wmax, w);
       }
+      // Models of different time per KiB share the launch by time, where it
+      // fills every workgroup; smaller launches are bound by their ranges'
+      // latency and stay cut as finely as the blocks allow.
+      g.weighted = wmin != wmax && !pl->whole_pages && T0w / maxcw >= (uint64_t)slots && T0w < (1ull << 31);
+      if (g.weighted) {
+        T0 = T0w;
+        maxc = maxcw;
+      }
+      const uint64_t fixed = kPieceFixedCost * (uint64_t)(g.weighted ? kTimeWeightUnit : 1);
+      auto cost = [&](int32_t i) {
+        const GeomK &k = gk[model_of(i)];
+        return (uint64_t)k.blk_cost * (uint64_t)(g.weighted ? time_weight(k.variant) : 1);
+      };
       const uint64_t W0 = std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)slots, T0 / maxc));
       uint64_t T = 0, pre0 = 0;
       for (size_t k = 0; k < g.idx.size(); ++k) {
         const int32_t i = g.idx[k];
-        const uint64_t c = (uint64_t)gk[model_of(i)].blk_cost;
+        const uint64_t c = cost(i);
         const bool straddled = k > 0 && (pre0 * W0) % T0 != 0;
-        T += straddled ? kPieceFixedCost : 0;
+        T += straddled ? fixed : 0;
         cost_prefix[i] = (uint32_t)std::min<uint64_t>(T, 0xFFFFFFFFull);  // the request's first block
         T += (uint64_t)blocks[i] * c;
         pre0 += (uint64_t)blocks[i] * c;
@@ -1125,7 +1162,7 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
       auto owner = [&](uint64_t x) { return (uint32_t)(((x + 1) * W - 1) / T); };
       for (int32_t i : g.idx) {
         // block j of the request sits at C + j c
-        const uint64_t c = (uint64_t)gk[model_of(i)].blk_cost, C = cost_prefix[i];
+        const uint64_t c = cost(i), C = cost_prefix[i];
         const uint32_t w0 = owner(C), w1 = owner(C + (uint64_t)(blocks[i] - 1) * c);
         first_worker[i] = (int32_t)w0;
         n_slots[i] = (int32_t)(w1 - w0 + 1);
@@ -1243,7 +1280,10 @@ cp_status launch_plan(cp_pool *p, const DecodePlan &pl, int32_t n, const int32_t
     a.schedule = o.schedule;
     a.total_cost = g.total_cost;
     a.n_units = (int32_t)g.n_units;
-    for (size_t k = 0; k < g.models.size(); ++k) a.geom[k] = pl.gk[g.models[k]];
+    for (size_t k = 0; k < g.models.size(); ++k) {
+      a.geom[k] = pl.gk[g.models[k]];
+      if (g.weighted) a.geom[k].blk_cost *= time_weight(a.geom[k].variant);
+    }
     for (int32_t i : g.idx) {
       const Request &r = p->st.req(req_ids[i]);
       DecReq &d = a.req[a.n_req++];
@@ -1524,6 +1564,7 @@ cp_status cp_attn_decode_noalloc(cp_pool *p, int32_t n, const int32_t *req_ids, 
   // workspace with them is made again of whole pages.
   uint64_t o_bytes = 0, need = 0;
   for (int whole_pages = 0; whole_pages < 2; ++whole_pages) {
+    pl.whole_pages = whole_pages != 0;
     if (whole_pages) set_blocks(p, &pl.gk, true);
     rc = plan_decode(p, n, req_ids, nullptr, &pl);
     if (rc) return rc;

@@ -89,3 +89,12 @@ def test_noalloc_falls_back_to_whole_pages():
     assert (l0 - l1).abs().max() <= 2 * LSE_MAX_ABS
     pool.close(rid)
     pool.destroy()
+
+
+def test_models_sharing_a_launch_by_time():
+    """Launches with work for every workgroup, of models whose kernels take
+    different times per byte: ranges of every length, boundaries of every
+    cost, with and without sub-page blocks."""
+    run([(gqa(40, 8), 6000), (mla(64), 2100), (mla(20), 1), (gqa(40, 8), 5003), (mla(20), 1501), (gqa(28, 4), 65)], 64,
+        BAL, 0)
+    run([(gqa(128, 1), 9000), (gqa(128, 2), 31), (gqa(128, 2), 8001), (gqa(64, 8), 7010), (gqa(128, 1), 64)], 64, BAL, 0)
