@@ -23,7 +23,8 @@
 //
 // Measured on 13 MQA-128 and 3 GQA-128:2 requests of 1K-64K tokens (183 MB of
 // KV): 42.7 us in one launch (4.3 TB/s; 45.1 with a barrier and a softmax
-// update per tile), where a workgroup of four waves that
+// update per tile; another 1.6 us less with the two group sizes sharing the
+// launch by time), where a workgroup of four waves that
 // split scores by heads and P.V by columns, with P and the rescale factors
 // going through LDS and two barriers per tile, took 66.5 and 37.4 us in a
 // launch per group size (about 4,300 cycles per tile, 512 of them products).
