@@ -12,6 +12,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "cost_line.hpp"
 #include "crosspool.h"
 #include "kargs.h"
 static_assert(cp::kNoAllocScratchBytes == CP_NOALLOC_WORKSPACE_BYTES, "the header states the fixed workspace size");
@@ -914,26 +915,6 @@ cp_status cp_attn_decode_ex(cp_pool *p, int32_t n, const int32_t *req_ids, const
 
 namespace {
 
-// Blocks of the balanced schedule's cost line. A block is a page, or for pages
-// of more than 128 KiB (unless `whole_pages`) what the kernel works through
-// in one step (six requests of groups of 1 to 4 heads, 128-1024 tokens,
-// 64-token pages of 128 and 256 KiB: 14.4 us a call against 19.4 with whole
-// pages; cutting 32 to 128 KiB pages too gained nothing and cost 1 to 4% on
-// batches that small, by more partials). Its relative work: its bytes, times
-// the head blocks that each reread it on the MLA vector path and on the
-// stream path.
-void set_blocks(cp_pool *p, std::vector<GeomK> *gk, bool whole_pages) {
-  const int32_t P = p->st.page_tokens();
-  for (int32_t m = 0; m < p->st.n_models(); ++m) {
-    const Geom &g = p->st.model(m);
-    GeomK &k = (*gk)[m];
-    const int32_t step = matrix_step_tokens(k.variant, g.hkv);
-    k.blk_tokens = !whole_pages && g.page_bytes > (128 << 10) && step > 0 && P % step == 0 ? step : P;
-    const int64_t kib = ((int64_t)k.blk_tokens * g.kappa + 1023) / 1024;
-    k.blk_cost = (int32_t)(kib * (g.kind == kMLA || is_stream(k.variant) ? k.nb : 1));
-  }
-}
-
 // Checks what every decode call needs; fills the options and the per-model
 // kernel geometry (variant, head blocking, page cost).
 cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const void *q, void *out, float *lse,
@@ -972,7 +953,6 @@ cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const vo
       choose_valu(g, &gk[m], P);
     }
   }
-  set_blocks(p, &gk, false);
   for (int32_t i = 0; i < n; ++i) {
     const int32_t m = p->st.req(req_ids[i]).model;
     if (o.path == CP_PATH_MFMA && matrix_variant(p->st.model(m), P) < 0)
@@ -982,11 +962,6 @@ cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const vo
   *gk_out = std::move(gk);
   return CP_OK;
 }
-
-// The balanced schedule's ranges hold no less than this (one MLA page of 64
-// tokens), or a page of models with smaller ones.
-constexpr uint64_t kMinRangeKib = 72;
-constexpr int32_t kTimeWeightUnit = 8;
 
 // Time per KiB of KV, in eighths of what the narrow and stream kernels take:
 // the kernels of more heads per KV byte run below HBM speed, and where they
@@ -1014,10 +989,10 @@ struct DecodePlan {
     int grid = 0;
     uint32_t total_cost = 0;
     uint32_t n_units = 0;
-    bool weighted = false;  // balanced: block costs times time_weight
+    std::vector<int32_t> blk_tokens, blk_cost;  // balanced, per entry of models
   };
   cp_decode_opts o{};
-  bool whole_pages = false;  // ranges of whole pages, shared by bytes
+  bool whole_pages = false;  // balanced: no ranges finer than pages
   std::vector<GeomK> gk;
   std::vector<int64_t> attend;  // tokens each request attends over (call order)
   std::vector<uint64_t> q_off, o_off, l_off;
@@ -1048,7 +1023,6 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
   pl->q_off.assign(n, 0);
   pl->o_off.assign(n, 0);
   pl->l_off.assign(n, 0);
-  std::vector<int64_t> blocks(n);  // balanced schedule: blocks of GeomK::blk_tokens tokens
   uint64_t qo = 0, oo = 0, lo = 0;
   for (int32_t i = 0; i < n; ++i) {
     const Geom &g = p->st.model(model_of(i));
@@ -1107,68 +1081,29 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
     const int wgs = wide ? 1 : decode_wgs_per_cu(g.mask);
     const int64_t slots = (int64_t)p->num_cus * wgs;
     if (o.schedule == CP_SCHED_BALANCED) {
-      // Every workgroup pays the fixed cost of its first piece, so the cost
-      // line charges kPieceFixedCost only where a request boundary falls
-      // inside a workgroup's share (that workgroup runs a second piece):
-      // not before the launch's first request, and not at a boundary that
-      // coincides with a share boundary of the line without fixed costs
-      // (equal requests over a multiple of their count of workgroups).
-      uint64_t T0 = 0, maxc = 1, T0w = 0, maxcw = 1;
-      int32_t wmin = 1 << 30, wmax = 0;
+      std::vector<LineReq> reqs;
       for (int32_t i : g.idx) {
+        const Geom &m = p->st.model(model_of(i));
         const GeomK &k = gk[model_of(i)];
-        const int32_t w = time_weight(k.variant);
-        const uint64_t c = (uint64_t)k.blk_cost;
-        blocks[i] = (pl->attend[i] + k.blk_tokens - 1) / k.blk_tokens;
-        T0 += (uint64_t)blocks[i] * c;
-        // a range spans at least a block of every model, and a page of those
-        // whose pages are smaller than kMinRangeKib (splitting further makes
-        // more partials without shortening the launch)
-        const uint64_t page = c * (uint64_t)(P / k.blk_tokens), least = std::max(c, std::min<uint64_t>(page, kMinRangeKib));
-        maxc = std::max(maxc, least);
-        T0w += (uint64_t)blocks[i] * c * (uint64_t)w;
-        maxcw = std::max(maxcw, least * (uint64_t)w);
-        wmin = std::min(wmin, w);
-        wmax = std::max(wmax, w);
+        // head blocks reread the KV on the MLA vector path and on the stream path
+        reqs.push_back(LineReq{pl->attend[i], P, matrix_step_tokens(k.variant, m.hkv), m.kappa,
+                               m.kind == kMLA || is_stream(k.variant) ? k.nb : 1, time_weight(k.variant)});
       }
-      // Models of different time per KiB share the launch by time, where it
-      // fills every workgroup; smaller launches are bound by their ranges'
-      // latency and stay cut as finely as the blocks allow.
-      g.weighted = wmin != wmax && !pl->whole_pages && T0w / maxcw >= (uint64_t)slots && T0w < (1ull << 31);
-      if (g.weighted) {
-        T0 = T0w;
-        maxc = maxcw;
-      }
-      const uint64_t fixed = kPieceFixedCost * (uint64_t)(g.weighted ? kTimeWeightUnit : 1);
-      auto cost = [&](int32_t i) {
-        const GeomK &k = gk[model_of(i)];
-        return (uint64_t)k.blk_cost * (uint64_t)(g.weighted ? time_weight(k.variant) : 1);
-      };
-      const uint64_t W0 = std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)slots, T0 / maxc));
-      uint64_t T = 0, pre0 = 0;
+      const Line ln = plan_line(reqs, (uint64_t)slots, pl->whole_pages);
+      if (ln.total > 0xFFFFFFFFull) return fail(CP_EINVAL, "batch too large for one launch");
+      g.blk_tokens.assign(g.models.size(), 1);
+      g.blk_cost.assign(g.models.size(), 1);
       for (size_t k = 0; k < g.idx.size(); ++k) {
         const int32_t i = g.idx[k];
-        const uint64_t c = cost(i);
-        const bool straddled = k > 0 && (pre0 * W0) % T0 != 0;
-        T += straddled ? fixed : 0;
-        cost_prefix[i] = (uint32_t)std::min<uint64_t>(T, 0xFFFFFFFFull);  // the request's first block
-        T += (uint64_t)blocks[i] * c;
-        pre0 += (uint64_t)blocks[i] * c;
+        first_worker[i] = ln.first[k];
+        n_slots[i] = ln.ranges[k];
+        cost_prefix[i] = (uint32_t)ln.begin[k];  // the request's first block
+        const size_t m = std::find(g.models.begin(), g.models.end(), model_of(i)) - g.models.begin();
+        g.blk_tokens[m] = ln.blk_tokens[k];
+        g.blk_cost[m] = ln.blk_cost[k];
       }
-      if (T > 0xFFFFFFFFull) return fail(CP_EINVAL, "batch too large for one launch");
-      // every range spans at least one block of any model, so no request has
-      // an empty slot between its first and last worker
-      const uint64_t W = std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)slots, T / maxc));
-      auto owner = [&](uint64_t x) { return (uint32_t)(((x + 1) * W - 1) / T); };
-      for (int32_t i : g.idx) {
-        // block j of the request sits at C + j c
-        const uint64_t c = cost(i), C = cost_prefix[i];
-        const uint32_t w0 = owner(C), w1 = owner(C + (uint64_t)(blocks[i] - 1) * c);
-        first_worker[i] = (int32_t)w0;
-        n_slots[i] = (int32_t)(w1 - w0 + 1);
-      }
-      g.grid = (int)W;
-      g.total_cost = (uint32_t)T;
+      g.grid = (int)ln.workers;
+      g.total_cost = (uint32_t)ln.total;
       if (g.grid > 0xFFFF) return fail(CP_EINVAL, "too many workers");
     } else {
       // queue / grid: page-aligned KV ranges of similar cost, about two per
@@ -1282,7 +1217,9 @@ cp_status launch_plan(cp_pool *p, const DecodePlan &pl, int32_t n, const int32_t
     a.n_units = (int32_t)g.n_units;
     for (size_t k = 0; k < g.models.size(); ++k) {
       a.geom[k] = pl.gk[g.models[k]];
-      if (g.weighted) a.geom[k].blk_cost *= time_weight(a.geom[k].variant);
+      if (o.schedule != CP_SCHED_BALANCED) continue;
+      a.geom[k].blk_tokens = g.blk_tokens[k];
+      a.geom[k].blk_cost = g.blk_cost[k];
     }
     for (int32_t i : g.idx) {
       const Request &r = p->st.req(req_ids[i]);
@@ -1565,7 +1502,6 @@ cp_status cp_attn_decode_noalloc(cp_pool *p, int32_t n, const int32_t *req_ids, 
   uint64_t o_bytes = 0, need = 0;
   for (int whole_pages = 0; whole_pages < 2; ++whole_pages) {
     pl.whole_pages = whole_pages != 0;
-    if (whole_pages) set_blocks(p, &pl.gk, true);
     rc = plan_decode(p, n, req_ids, nullptr, &pl);
     if (rc) return rc;
     o_bytes = (pl.ws_elems * sizeof(uint16_t) + 255) / 256 * 256;

@@ -20,7 +20,7 @@ constexpr int32_t kStackCap = 8192;
 // most) when a step needs more than it holds.
 constexpr int32_t kStackRefill = 1024;
 enum : int32_t { kSchedBalanced = 0, kSchedQueue = 1, kSchedGrid = 2 };
-// Balanced schedule. The cost line counts KiB of KV; a request's stretch of it
+// Balanced schedule (cost_line.hpp). A request's stretch of the launch's cost line
 // is cut between blocks of GeomK::blk_tokens tokens: pages, or for large pages
 // the tokens that the model's kernel works through in one step of its loop.
 // The fixed work of one piece (page-table and query loads, the latency of its

@@ -1,0 +1,132 @@
+"""The balanced schedule's plan of a launch (cost_line.hpp, compiled here with
+g++): every block of every request lies in exactly one range, no range is
+empty, and batches of whole pages are cut where a line of 8 KiB units cuts
+them."""
+import ctypes
+import os
+import random
+import shutil
+import subprocess
+from dataclasses import dataclass
+
+import pytest
+
+from paper_2606_24506_amd import build
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no C++ compiler")
+
+
+@dataclass(frozen=True)
+class Model:
+    kappa: int        # KV bytes per token
+    step: int         # tokens the kernel works through at once
+    weight: int = 8   # time per KiB, eighths
+    out: int = 0      # output elements of a request
+    rereads: int = 1
+
+
+# kinds of models with the steps and weights of their kernels
+MLA16 = Model(1152, 64, out=16 * 512)
+MLA20 = Model(1152, 64, 12, 20 * 512)
+MLA64 = Model(1152, 32, 18, 64 * 512)
+MLA200 = Model(1152, 32, 18, 200 * 512, 4)
+MQA32 = Model(512, 128, out=32 * 128)
+MQA128 = Model(512, 32, 10, 128 * 128)
+GQA32X4 = Model(2048, 32, out=32 * 128)
+GQA32X8 = Model(4096, 16, out=32 * 128)
+GQA64X8 = Model(4096, 32, out=64 * 128)
+GQA16X4D64 = Model(1024, 64, out=16 * 64)
+SLOTS = 256
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("cost_line") / "shim.so")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "c", "cost_line_shim.cpp")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-shared", "-fPIC", "-I", build.CSRC, src, "-o", out],
+                   check=True)
+    lib = ctypes.CDLL(out)
+    lib.cost_line.restype = ctypes.c_int64
+    return lib
+
+
+def plan(lib, reqs, page_tokens=64, slots=SLOTS, whole=False):
+    """reqs: [(Model, tokens)] -> (workers, total, [(blk_tokens, blk_cost, begin, first, ranges)])"""
+    n = len(reqs)
+    i32 = lambda v: (ctypes.c_int32 * n)(*v)
+    out, total = (ctypes.c_int64 * (5 * n))(), ctypes.c_int64()
+    w = lib.cost_line(n, (ctypes.c_int64 * n)(*[t for _, t in reqs]), i32([page_tokens] * n), i32([m.step for m, _ in reqs]),
+                      i32([m.kappa for m, _ in reqs]), i32([m.rereads for m, _ in reqs]), i32([m.weight for m, _ in reqs]),
+                      slots, int(whole), out, ctypes.byref(total))
+    return w, total.value, [tuple(out[5 * i:5 * i + 5]) for i in range(n)]
+
+
+def pieces(reqs, ln):
+    """[(request, worker, first token, end token)], as the kernels find them."""
+    workers, total, per = ln
+    got = []
+    for r, ((_, tokens), (blk, cost, begin, first, ranges)) in enumerate(zip(reqs, per)):
+        nb = -(-tokens // blk)
+        for w in range(max(0, first - 1), min(workers, first + ranges + 1)):
+            lo, hi = w * total // workers, (w + 1) * total // workers
+            jb = max(0, -(-(lo - begin) // cost))
+            je = min(nb, -(-(hi - begin) // cost)) if begin < hi else 0
+            if jb < je:
+                got.append((r, w, jb * blk, min(tokens, je * blk)))
+        assert [w for q, w, _, _ in got if q == r] == list(range(first, first + ranges))
+    return got
+
+
+def whole_pages_by_8_kib(reqs, page_tokens, slots=SLOTS):
+    """Ranges per request of a line of 8 KiB units, worked out from its definition."""
+    cost = [page_tokens * m.kappa // 8192 * m.rereads for m, _ in reqs]
+    nb = [-(-t // page_tokens) for _, t in reqs]
+    bare = sum(c * k for c, k in zip(cost, nb))
+    w0 = max(1, min(slots, bare // max(cost)))
+    begin, at, pre = [], 0, 0
+    for i, (c, k) in enumerate(zip(cost, nb)):
+        if i and pre * w0 % bare:
+            at += 40
+        begin.append(at)
+        at += c * k
+        pre += c * k
+    workers = max(1, min(slots, at // max(cost)))
+    share = [w * at // workers for w in range(workers + 1)]
+    got = []
+    for r, (c, k, b) in enumerate(zip(cost, nb, begin)):
+        for w in range(workers):
+            pages = [j for j in range(k) if share[w] <= b + j * c < share[w + 1]] if b + k * c > share[w] else []
+            if pages:
+                got.append((r, w, pages[0] * page_tokens, min(reqs[r][1], (pages[-1] + 1) * page_tokens)))
+    return got
+
+
+def random_batch(rng, models, n, hi):
+    return [(rng.choice(models), int(2 ** rng.uniform(0, hi))) for _ in range(n)]
+
+
+@pytest.mark.parametrize("models,page_tokens", [
+    ([MLA16], 64), ([MLA16, MQA32, GQA32X4], 64), ([MLA16], 32), ([MLA16], 128), ([GQA32X8], 64), ([GQA64X8, MQA32], 64),
+    ([GQA32X8, GQA16X4D64], 64), ([MLA20, MLA64, GQA32X8], 64), ([MQA128, GQA32X4], 64), ([MLA200], 128), ([MQA32], 1)])
+def test_ranges_cover_every_request_once(shim, models, page_tokens):
+    rng = random.Random(1)
+    for k in range(60):
+        reqs = random_batch(rng, models, rng.randint(1, 64), 14)
+        for whole in (False, True):
+            ln = plan(shim, reqs, page_tokens, slots=rng.choice([1, 7, 256]), whole=whole)
+            assert ln[1] < 1 << 32
+            at = [0] * len(reqs)
+            for r, _, lo, hi in pieces(reqs, ln):
+                assert lo == at[r] and hi > lo
+                at[r] = hi
+            assert at == [t for _, t in reqs]
+
+
+@pytest.mark.parametrize("models,page_tokens", [([MLA16], 64), ([MLA16, MQA32, GQA32X4], 64), ([MQA32, GQA32X4], 32)])
+def test_pages_of_8_kib_multiples_keep_their_ranges(shim, models, page_tokens):
+    """Launches that nothing makes finer: the ranges, and so the bits of the
+    results, are those of a line that counts 8 KiB units."""
+    rng = random.Random(2)
+    for k in range(40):
+        reqs = random_batch(rng, models, rng.randint(1, 64), 15)
+        assert pieces(reqs, plan(shim, reqs, page_tokens)) == whole_pages_by_8_kib(reqs, page_tokens)
