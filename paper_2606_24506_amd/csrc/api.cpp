@@ -993,6 +993,7 @@ struct DecodePlan {
   };
   cp_decode_opts o{};
   bool whole_pages = false;  // balanced: no ranges finer than pages
+  bool finer = false;        // ... some launch has such ranges
   std::vector<GeomK> gk;
   std::vector<int64_t> attend;  // tokens each request attends over (call order)
   std::vector<uint64_t> q_off, o_off, l_off;
@@ -1002,17 +1003,21 @@ struct DecodePlan {
   uint64_t ws_rows = 0, ws_elems = 0;  // partial lse rows and partial output elements
   uint16_t *ws_o = nullptr;            // bound by the caller before launch
   float *ws_l = nullptr;
+  // Bytes of the partial outputs and, aligned behind them, of the lse values.
+  uint64_t ws_o_bytes() const { return (ws_elems * sizeof(uint16_t) + 255) / 256 * 256; }
+  uint64_t ws_bytes() const { return ws_o_bytes() + ws_rows * sizeof(float); }
 };
 
 // Plans a decode over requests whose attended lengths are their current
 // ones plus extra[i] (tokens a fused step places before the launch; NULL:
-// none). pl->o and pl->gk come from decode_prepare. Runs every capacity
-// check of the call; changes nothing.
-cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32_t *extra, DecodePlan *pl) {
+// none), with or without pl->whole_pages. pl->o and pl->gk come from
+// decode_prepare. Runs every capacity check of the call; changes nothing.
+cp_status plan_ranges(cp_pool *p, int32_t n, const int32_t *req_ids, const int32_t *extra, DecodePlan *pl) {
   const cp_decode_opts &o = pl->o;
   const std::vector<GeomK> &gk = pl->gk;
   const int32_t P = p->st.page_tokens();
   auto model_of = [&](int32_t i) { return p->st.req(req_ids[i]).model; };
+  pl->finer = false;
   pl->attend.assign(n, 0);
   for (int32_t i = 0; i < n; ++i) {
     pl->attend[i] = p->st.req(req_ids[i]).attend_len() + (extra ? extra[i] : 0);
@@ -1090,6 +1095,7 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
                                m.kind == kMLA || is_stream(k.variant) ? k.nb : 1, time_weight(k.variant)});
       }
       const Line ln = plan_line(reqs, (uint64_t)slots, pl->whole_pages);
+      pl->finer = pl->finer || ln.finer;
       if (ln.total > 0xFFFFFFFFull) return fail(CP_EINVAL, "batch too large for one launch");
       g.blk_tokens.assign(g.models.size(), 1);
       g.blk_cost.assign(g.models.size(), 1);
@@ -1165,6 +1171,19 @@ cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
   pl->ws_rows = ws_rows;
   pl->ws_elems = ws_elems;
   return CP_OK;
+}
+
+// The plan of every decode call. Ranges finer than pages make more partials:
+// a plan that outgrows the fixed workspace with them is made again of whole
+// pages (200 MLA heads on 150 pages of 144 KiB: 52 MB cut inside pages, 31 MB
+// of whole ones), whichever workspace the call then uses, so that
+// cp_attn_decode_noalloc and the other calls plan alike.
+cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32_t *extra, DecodePlan *pl) {
+  pl->whole_pages = false;
+  cp_status rc = plan_ranges(p, n, req_ids, extra, pl);
+  if (rc || !pl->finer || pl->ws_bytes() <= kNoAllocScratchBytes) return rc;
+  pl->whole_pages = true;
+  return plan_ranges(p, n, req_ids, extra, pl);
 }
 
 // Binds the pool's own split workspace to a plan, growing it if needed.
@@ -1496,18 +1515,9 @@ cp_status cp_attn_decode_noalloc(cp_pool *p, int32_t n, const int32_t *req_ids, 
   DecodePlan pl;
   cp_status rc = decode_prepare(p, n, req_ids, q, out, lse, opts, &pl.o, &pl.gk);
   if (rc) return rc;
-  // Partial outputs first, then the partial lse values (256-byte aligned).
-  // Ranges cut inside pages make more partials: a plan that outgrows the
-  // workspace with them is made again of whole pages.
-  uint64_t o_bytes = 0, need = 0;
-  for (int whole_pages = 0; whole_pages < 2; ++whole_pages) {
-    pl.whole_pages = whole_pages != 0;
-    rc = plan_decode(p, n, req_ids, nullptr, &pl);
-    if (rc) return rc;
-    o_bytes = (pl.ws_elems * sizeof(uint16_t) + 255) / 256 * 256;
-    need = o_bytes + pl.ws_rows * sizeof(float);
-    if (need <= kNoAllocScratchBytes) break;
-  }
+  rc = plan_decode(p, n, req_ids, nullptr, &pl);
+  if (rc) return rc;
+  const uint64_t need = pl.ws_bytes();
   if (need > kNoAllocScratchBytes)
     return fail(CP_EINVAL,
                 "the split plan needs %llu bytes of workspace; cp_attn_decode_noalloc has %llu (use fewer KV ranges: "
@@ -1519,7 +1529,7 @@ cp_status cp_attn_decode_noalloc(cp_pool *p, int32_t n, const int32_t *req_ids, 
     hipError_t e = scratch_device_address(p->device, &base);
     if (e != hipSuccess) return hip_fail(e, "address of the fixed split workspace");
     pl.ws_o = static_cast<uint16_t *>(base);
-    pl.ws_l = reinterpret_cast<float *>(static_cast<uint8_t *>(base) + o_bytes);
+    pl.ws_l = reinterpret_cast<float *>(static_cast<uint8_t *>(base) + pl.ws_o_bytes());
   }
   return launch_plan(p, pl, n, req_ids, q, out, lse, hip_stream, nullptr, nullptr);
 }

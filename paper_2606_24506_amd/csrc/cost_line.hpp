@@ -35,6 +35,7 @@ struct Line {
   std::vector<uint64_t> begin;
   uint64_t total = 0;
   uint32_t workers = 0;
+  bool finer = false;  // cut inside pages, or shared by time
 };
 
 // Lays out blocks of the given sizes and costs. Every workgroup pays the
@@ -138,6 +139,7 @@ inline Line fine_line(const std::vector<LineReq> &reqs, uint64_t slots) {
     return ln;
   }
   lay_line(reqs, fixed, least, slots, &ln);
+  ln.finer = true;
   return ln;
 }
 

@@ -7,7 +7,6 @@ import pytest
 import torch
 
 from paper_2606_24506_amd import crosspool as cpl
-from parity import LSE_MAX_ABS, OUT_REL_L2
 from test_gpu_head_counts import BAL, gqa, mla, run
 from workloads.harness import to_device_u16
 
@@ -65,29 +64,35 @@ def test_fused_step_over_ranges_inside_pages(model, page_tokens):
         assert torch.equal(o0, o1) and torch.equal(l0.view(torch.int32), l1.view(torch.int32))
 
 
-def test_noalloc_falls_back_to_whole_pages():
-    """200 MLA heads, pages of 144 KiB, 150 pages: cut inside pages the call has
-    256 ranges (52 MB of partials), of whole pages 150 (31 MB), which the fixed
-    40 MiB workspace holds. Both plans are within the oracle's bar of the same
-    result, so they differ by no more than twice that."""
-    model, n, P = mla(200), 150 * 128, 128
-    g = torch.Generator(device="cuda").manual_seed(4)
-    rows = torch.randn(n * model.row_width, device="cuda", generator=g).to(torch.bfloat16).view(torch.int16)
-    q = torch.randn(model.n_q_heads * model.d_k, device="cuda", generator=g).to(torch.bfloat16).view(torch.int16)
-    pool = cpl.Pool(page_tokens=P, pool_bytes=64 << 20, placement_seed=2, device=0)
-    rid = pool.open(pool.register_spec(model), n)
-    pool.append([rid], [n], rows)
+@pytest.mark.parametrize("specs_lens,page_tokens", [
+    # pages of 144 KiB: cut inside pages the call has 256 ranges (52 MB of
+    # partials), of whole pages 150 (31 MB)
+    ([(mla(200), 150 * 128)], 128),
+    # shared by time, and by bytes, every workgroup has a range of each model
+    ([(mla(200), 140 * 128), (gqa(40, 8), 700)], 128),
+    ([(gqa(32, 8), 700), (mla(64), 900)], 64)], ids=["mla200", "mla200+gqa40", "within"])
+def test_noalloc_plans_as_decode_does(specs_lens, page_tokens):
+    """The fixed 40 MiB workspace holds the partials of these batches on ranges
+    of whole pages, not of finer ones (or, the last one, holds both): the call
+    is accepted and its results are decode's, bit for bit."""
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    bits = lambda k: torch.randn(k, device="cuda", generator=gen).to(torch.bfloat16).view(torch.int16)
+    pool = cpl.Pool(page_tokens=page_tokens, pool_bytes=128 << 20, placement_seed=2, device=0)
+    rids = []
+    for m, n in specs_lens:
+        rids.append(pool.open(pool.register_spec(m), n))
+        pool.append([rids[-1]], [n], bits(n * m.row_width))
+    q = bits(sum(m.n_q_heads * m.d_k for m, _ in specs_lens))
     res = []
     for call in (pool.decode, pool.decode_noalloc):
-        out = torch.zeros(model.n_q_heads * model.d_v, dtype=torch.int16, device="cuda")
-        lse = torch.zeros(model.n_q_heads, dtype=torch.float32, device="cuda")
-        call([rid], q, out, lse)
+        out = torch.zeros(sum(m.n_q_heads * m.d_v for m, _ in specs_lens), dtype=torch.int16, device="cuda")
+        lse = torch.zeros(sum(m.n_q_heads for m, _ in specs_lens), dtype=torch.float32, device="cuda")
+        call(rids, q, out, lse)
         torch.cuda.synchronize()
-        res.append((out.view(torch.bfloat16).double(), lse.double()))
-    (o0, l0), (o1, l1) = res
-    assert torch.linalg.norm(o0 - o1) <= 2 * OUT_REL_L2 * torch.linalg.norm(o0)
-    assert (l0 - l1).abs().max() <= 2 * LSE_MAX_ABS
-    pool.close(rid)
+        res.append((out, lse))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1].view(torch.int32), res[1][1].view(torch.int32))
+    for r in rids:
+        pool.close(r)
     pool.destroy()
 
 
