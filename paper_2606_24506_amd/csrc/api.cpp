@@ -866,11 +866,15 @@ int32_t units_per_range(const Geom &g, const GeomK &k) {
   return g.hkv * k.nb;
 }
 
-// Split workspace: o_elems bf16 partial outputs and l_floats fp32 partial
-// lse values.
+// Bytes of a pool's split workspace: o_elems bf16 partial outputs and l_floats
+// fp32 partial lse values.
+uint64_t pool_ws_bytes(uint64_t o_elems, uint64_t l_floats) {
+  return o_elems * sizeof(uint16_t) + l_floats * sizeof(float);
+}
+
 cp_status ensure_ws(cp_pool *p, uint64_t o_elems, uint64_t l_floats) {
   if (o_elems <= p->ws_o_cap && l_floats <= p->ws_l_cap) return CP_OK;
-  const uint64_t need_bytes = o_elems * sizeof(uint16_t) + l_floats * sizeof(float);
+  const uint64_t need_bytes = pool_ws_bytes(o_elems, l_floats);
   if (p->ws_limit && need_bytes > p->ws_limit)
     return fail(CP_ENOMEM, "the split plan needs %llu bytes of workspace, past the pool's cap of %llu",
                 (unsigned long long)need_bytes, (unsigned long long)p->ws_limit);
@@ -1174,14 +1178,16 @@ cp_status plan_ranges(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
 }
 
 // The plan of every decode call. Ranges finer than pages make more partials:
-// a plan that outgrows the fixed workspace with them is made again of whole
-// pages (200 MLA heads on 150 pages of 144 KiB: 52 MB cut inside pages, 31 MB
-// of whole ones), whichever workspace the call then uses, so that
+// a plan that outgrows the fixed workspace or the pool's cap with them is made
+// again of whole pages (200 MLA heads on 150 pages of 144 KiB: 52 MB cut inside
+// pages, 31 MB of whole ones), whichever workspace the call then uses, so that
 // cp_attn_decode_noalloc and the other calls plan alike.
 cp_status plan_decode(cp_pool *p, int32_t n, const int32_t *req_ids, const int32_t *extra, DecodePlan *pl) {
   pl->whole_pages = false;
   cp_status rc = plan_ranges(p, n, req_ids, extra, pl);
-  if (rc || !pl->finer || pl->ws_bytes() <= kNoAllocScratchBytes) return rc;
+  const bool fits = pl->ws_bytes() <= kNoAllocScratchBytes &&
+                    (!p->ws_limit || pool_ws_bytes(pl->ws_elems, pl->ws_rows) <= p->ws_limit);
+  if (rc || !pl->finer || fits) return rc;
   pl->whole_pages = true;
   return plan_ranges(p, n, req_ids, extra, pl);
 }

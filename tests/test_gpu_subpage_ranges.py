@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from paper_2606_24506_amd import crosspool as cpl
+from parity import LSE_MAX_ABS, OUT_REL_L2
 from test_gpu_head_counts import BAL, gqa, mla, run
 from workloads.harness import to_device_u16
 
@@ -94,6 +95,43 @@ def test_noalloc_plans_as_decode_does(specs_lens, page_tokens):
     for r in rids:
         pool.close(r)
     pool.destroy()
+
+
+def test_capped_workspace_falls_back_to_whole_pages():
+    """Six 300-token requests on 256 KiB pages: 30 ranges of whole pages, about
+    120 cut inside them. A pool whose max_workspace_bytes holds the partials
+    of 30 takes every decode call, with one plan for all of them, and the
+    result of a pool without a cap (each within the oracle's bars, so within
+    twice that of one another)."""
+    m, n, k = gqa(32, 8), 300, 6
+    cap = 30 * m.n_q_heads * (2 * m.d_v + 4)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    bits = lambda c: torch.randn(c, device="cuda", generator=gen).to(torch.bfloat16).view(torch.int16)
+    rows, q = [bits(n * m.row_width) for _ in range(k)], bits(k * m.n_q_heads * m.d_k)
+    res = []
+    for limit in (cap, 0):
+        pool = cpl.Pool(page_tokens=64, pool_bytes=64 << 20, placement_seed=2, device=0, max_workspace_bytes=limit)
+        mid = pool.register_spec(m)
+        ids = [pool.open(mid, n + 8) for _ in range(k)]
+        for r, x in zip(ids, rows):
+            pool.append([r], [n], x)
+        calls = [pool.decode, pool.decode_noalloc, lambda *a: pool.decode_step(ids, [0] * k, None, *a[1:]),
+                 lambda *a: pool.decode_layers(ids, [0] * k, None, *a[1:])]
+        for call in calls:
+            out = torch.zeros(k * m.n_q_heads * m.d_v, dtype=torch.int16, device="cuda")
+            lse = torch.zeros(k * m.n_q_heads, dtype=torch.float32, device="cuda")
+            call(ids, q, out, lse)
+            torch.cuda.synchronize()
+            res.append((out, lse))
+        for r in ids:
+            pool.close(r)
+        pool.destroy()
+    for g in (res[:4], res[4:]):
+        for o, l in g[1:]:
+            assert torch.equal(o, g[0][0]) and torch.equal(l.view(torch.int32), g[0][1].view(torch.int32))
+    (o0, l0), (o1, l1) = [(o.view(torch.bfloat16).double(), l.double()) for o, l in (res[0], res[4])]
+    assert torch.linalg.norm(o0 - o1) <= 2 * OUT_REL_L2 * torch.linalg.norm(o1)
+    assert (l0 - l1).abs().max() <= 2 * LSE_MAX_ABS
 
 
 def test_models_sharing_a_launch_by_time():
