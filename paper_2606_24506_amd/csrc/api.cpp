@@ -1090,15 +1090,17 @@ cp_status plan_ranges(cp_pool *p, int32_t n, const int32_t *req_ids, const int32
     const int wgs = wide ? 1 : decode_wgs_per_cu(g.mask);
     const int64_t slots = (int64_t)p->num_cus * wgs;
     if (o.schedule == CP_SCHED_BALANCED) {
-      std::vector<LineReq> reqs;
+      LineReqs reqs;
       for (int32_t i : g.idx) {
         const Geom &m = p->st.model(model_of(i));
         const GeomK &k = gk[model_of(i)];
         // head blocks reread the KV on the MLA vector path and on the stream path
-        reqs.push_back(LineReq{pl->attend[i], P, matrix_step_tokens(k.variant, m.hkv), m.kappa,
-                               m.kind == kMLA || is_stream(k.variant) ? k.nb : 1, time_weight(k.variant)});
+        reqs.r[reqs.n++] = LineReq{pl->attend[i], P, matrix_step_tokens(k.variant, m.hkv), m.kappa,
+                               m.kind == kMLA || is_stream(k.variant) ? k.nb : 1, time_weight(k.variant),
+                               (uint32_t)(m.hq * m.d_v)};
       }
-      const Line ln = plan_line(reqs, (uint64_t)slots, pl->whole_pages);
+      Line ln;
+      plan_line(reqs, (uint64_t)slots, pl->whole_pages, &ln);
       pl->finer = pl->finer || ln.finer;
       if (ln.total > 0xFFFFFFFFull) return fail(CP_EINVAL, "batch too large for one launch");
       g.blk_tokens.assign(g.models.size(), 1);

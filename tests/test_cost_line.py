@@ -1,7 +1,7 @@
 """The balanced schedule's plan of a launch (cost_line.hpp, compiled here with
 g++): every block of every request lies in exactly one range, no range is
-empty, and batches of whole pages are cut where a line of 8 KiB units cuts
-them."""
+empty, batches of whole pages are cut where a line of 8 KiB units cuts them,
+and finer ranges are taken only where they shorten the longest share."""
 import ctypes
 import os
 import random
@@ -57,7 +57,7 @@ def plan(lib, reqs, page_tokens=64, slots=SLOTS, whole=False):
     out, total = (ctypes.c_int64 * (5 * n))(), ctypes.c_int64()
     w = lib.cost_line(n, (ctypes.c_int64 * n)(*[t for _, t in reqs]), i32([page_tokens] * n), i32([m.step for m, _ in reqs]),
                       i32([m.kappa for m, _ in reqs]), i32([m.rereads for m, _ in reqs]), i32([m.weight for m, _ in reqs]),
-                      slots, int(whole), out, ctypes.byref(total))
+                      i32([m.out for m, _ in reqs]), slots, int(whole), out, ctypes.byref(total))
     return w, total.value, [tuple(out[5 * i:5 * i + 5]) for i in range(n)]
 
 
@@ -130,3 +130,37 @@ def test_pages_of_8_kib_multiples_keep_their_ranges(shim, models, page_tokens):
     for k in range(40):
         reqs = random_batch(rng, models, rng.randint(1, 64), 15)
         assert pieces(reqs, plan(shim, reqs, page_tokens)) == whole_pages_by_8_kib(reqs, page_tokens)
+
+
+def longest_share(reqs, ln):
+    """KiB-times of the workgroup that has most, each piece with its fixed cost."""
+    share = {}
+    for r, w, lo, hi in pieces(reqs, ln):
+        m = reqs[r][0]
+        share[w] = share.get(w, 0) + (hi - lo) * m.kappa * m.rereads * m.weight / 8 / 1024 + 320
+    return max(share.values())
+
+
+@pytest.mark.parametrize("models,page_tokens,hi", [
+    ([MLA16], 128, 11), ([GQA64X8], 64, 12), ([GQA32X8, GQA16X4D64], 64, 11), ([MLA20, MLA64, GQA32X8], 64, 12),
+    ([MQA128, GQA32X4], 64, 14), ([MLA200], 128, 10), ([MLA16, MQA32, GQA32X4], 128, 12),
+    ([Model(512, 8, out=64), Model(65536, 8, out=64)], 16, 10)])
+def test_finer_ranges_never_lengthen_the_longest_share(shim, models, page_tokens, hi):
+    rng = random.Random(3)
+    finer = 0
+    for k in range(120):
+        reqs = random_batch(rng, models, rng.randint(1, 48), hi)
+        ln, whole = plan(shim, reqs, page_tokens), plan(shim, reqs, page_tokens, whole=True)
+        if ln != whole:
+            finer += 1
+            assert longest_share(reqs, ln) < longest_share(reqs, whole)
+    assert finer > 0
+
+
+def test_half_pages_are_not_cut_for_nothing(shim):
+    """MLA-16 on 128-token pages (two blocks each), half a page to a page for
+    every workgroup: cut, the longest share stays a page, or grows to three
+    blocks, and there are more partials."""
+    for lens in ([18000 // 16] * 16, [28000 // 16] * 16, [1100] * 16, [140 * k for k in range(1, 18)]):
+        reqs = [(MLA16, t) for t in lens]
+        assert plan(shim, reqs, 128) == plan(shim, reqs, 128, whole=True)
