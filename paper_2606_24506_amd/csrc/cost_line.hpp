@@ -149,9 +149,9 @@ inline bool fine_line(const LineReqs &rs, uint64_t slots, Line *ln) {
 
 // What a line's launch is expected to take: the longest share, in byte-times
 // (a byte of a model of weight kTimeWeightUnit takes that many), with the fixed
-// cost of every piece; and the partial outputs of its split requests.
+// cost of every piece; the outputs of its split requests, and their partials.
 struct LineTime {
-  uint64_t longest = 0, partials = 0;
+  uint64_t longest = 0, partials = 0, split = 0;
 };
 inline LineTime line_time(const LineReqs &rs, const Line &ln) {
   LineTime t;
@@ -189,7 +189,10 @@ inline LineTime line_time(const LineReqs &rs, const Line &ln) {
       share += (uint64_t)toks * tok_time + (uint64_t)kPieceFixedCost * 1024 * kTimeWeightUnit;
       j = je;
     }
-    if (ln.ranges[i] > 1) t.partials += (uint64_t)ln.ranges[i] * r.out_elems;
+    if (ln.ranges[i] > 1) {
+      t.partials += (uint64_t)ln.ranges[i] * r.out_elems;
+      t.split += r.out_elems;
+    }
   }
   t.longest = std::max(t.longest, share);
   return t;
@@ -204,6 +207,12 @@ inline LineTime line_time(const LineReqs &rs, const Line &ln) {
 // call of whole pages, always finer): 30 requests of 32K tokens in all 22.1,
 // 26.0; 16 of 18K 17.8, 19.0; but 16 of 32K 22.4, 21.1. GQA-64:8, 8 requests of
 // 16K tokens: 25.5, 27.4. In each the shorter longest share is the faster call.
+//
+// Partial outputs are bf16. A request in one range is summed in fp32 throughout,
+// one in several is rounded twice, however many they are (2.3e-3 relative
+// instead of 1.7e-3). More ranges are therefore not taken where they split
+// requests that whole pages leave in one piece, counted by outputs. (With as
+// many ranges it is chance which requests straddle a boundary.)
 inline void plan_line(const LineReqs &rs, uint64_t slots, bool whole_pages, Line *ln) {
   whole_page_line(rs, slots, ln);
   bool finer = false;
@@ -213,7 +222,8 @@ inline void plan_line(const LineReqs &rs, uint64_t slots, bool whole_pages, Line
   if (!fine_line(rs, slots, &f)) return;
   const LineTime tw = line_time(rs, *ln), tf = line_time(rs, f);
   const uint64_t more = tf.partials > tw.partials ? (tf.partials - tw.partials) * 4 * kTimeWeightUnit / f.workers : 0;
-  if (tf.longest + more < tw.longest) *ln = f;
+  const bool rounds_more = f.workers > ln->workers && tf.split > tw.split;
+  if (tf.longest + more < tw.longest && !rounds_more) *ln = f;
 }
 
 }  // namespace cp

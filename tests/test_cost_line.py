@@ -157,6 +157,28 @@ def test_finer_ranges_never_lengthen_the_longest_share(shim, models, page_tokens
     assert finer > 0
 
 
+def split_outputs(reqs, ln):
+    return sum(m.out for (m, _), p in zip(reqs, ln[2]) if p[4] > 1)
+
+
+@pytest.mark.parametrize("models,page_tokens,hi", [
+    ([MLA16], 128, 10), ([GQA64X8], 64, 9), ([GQA32X8, GQA16X4D64], 64, 10), ([MLA20, MLA64, GQA32X8], 64, 9)])
+def test_more_ranges_split_no_more_outputs(shim, models, page_tokens, hi):
+    """Short batches: a request summed in one piece on whole pages is not cut
+    into bf16 partials for the sake of more ranges."""
+    rng = random.Random(4)
+    finer = 0
+    for k in range(150):
+        reqs = random_batch(rng, models, rng.randint(1, 12), hi)
+        ln, whole = plan(shim, reqs, page_tokens), plan(shim, reqs, page_tokens, whole=True)
+        if ln[0] > whole[0]:
+            finer += 1
+            assert split_outputs(reqs, ln) <= split_outputs(reqs, whole)
+    assert finer > 0
+    one_page = [(models[0], page_tokens - 1)] * 6
+    assert split_outputs(one_page, plan(shim, one_page, page_tokens)) == 0
+
+
 def test_half_pages_are_not_cut_for_nothing(shim):
     """MLA-16 on 128-token pages (two blocks each), half a page to a page for
     every workgroup: cut, the longest share stays a page, or grows to three
