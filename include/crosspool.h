@@ -302,8 +302,12 @@ cp_status cp_attn_decode(cp_pool *pool, int32_t n, const int32_t *req_ids, const
                          void *hip_stream);
 
 typedef enum {
-  CP_PATH_AUTO = 0, /* matrix cores where a kernel for the geometry exists (P kept to 17 bits or, with 8, 16, 32, 64 or
-                       128 query heads per KV head, to bf16), vector otherwise */
+  /* Matrix cores where a kernel for the geometry exists, vector otherwise.
+   * The probabilities are multiplied as bf16 numbers for MLA with 16 or 128
+   * heads and for groups of 8, 16, 32, 64 or 128 query heads per KV head of
+   * width 128 (pages of a multiple of 32 tokens; MLA-16, and MLA-32 on
+   * others: of 16), and in fp32 precision for every other geometry. */
+  CP_PATH_AUTO = 0,
   CP_PATH_VALU = 1, /* force the vector (wavefront-reduction) kernel for every model */
   CP_PATH_MFMA = 2  /* force the matrix-core kernel for every model */
 } cp_path;

@@ -803,7 +803,7 @@ void choose_valu(const Geom &g, GeomK *k, int32_t P) {
 
 constexpr int32_t kMatrixFirst = 16;  // variants from here on run on the matrix cores
 
-// Matrix-core variant that keeps P to 2^-17 (two bf16 operands) for a model
+// Matrix-core variant that keeps P whole (three bf16 operands) for a model
 // without a matrix variant of its own, or -1; *nb: units per KV head and KV
 // range. The automatic path takes one wherever the geometry and page size fit:
 //   GQA / MHA, head_dim 64 or 128 (slices of 32 or 16 tokens must tile the

@@ -116,6 +116,23 @@ CP_DEV float xor_sum_16_32(float x) {
   return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
+// A probability as the sum of three bf16 numbers, exactly: its leading 8
+// mantissa bits, the next 8 of what is left, and the rest (at most 8). Each is in
+// the upper half of its word. The two rests are kept above zero, so that an
+// infinite V gives an infinite product as it does in fp32, and not 0 * inf.
+struct Bf16Parts {
+  uint32_t hi, mid, lo;
+};
+CP_DEV Bf16Parts split_bf16(float p) {
+  const uint32_t hi = __float_as_uint(p) & 0xFFFF0000u;
+  const float r1 = __builtin_fmaxf(p - __uint_as_float(hi), 1e-37f);
+  const uint32_t mid = __float_as_uint(r1) & 0xFFFF0000u;
+  const float r2 = __builtin_fmaxf(r1 - __uint_as_float(mid), 1e-37f);
+  return Bf16Parts{hi, mid, __float_as_uint(r2)};
+}
+// The upper halves of two words, b's above a's.
+CP_DEV uint32_t upper_halves(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xFFFF0000u); }
+
 // Lane index and its mfma coordinates, counted afresh by the lane-count
 // instructions at every use: the compiler can neither hoist them nor keep
 // the thread index alive across the loop for them. A unit that takes its

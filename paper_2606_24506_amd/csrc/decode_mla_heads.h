@@ -15,19 +15,19 @@
 // free here; splitting the scores instead would put P through LDS behind a
 // second barrier.
 //
-// P stays a 32-bit quantity: P.V takes it as the sum of two bf16 operands (cut
-// and rest, at most 2^-17 of p left out; the rest is kept above zero so that
-// an infinite V stays infinite), because these head counts otherwise run on
-// the vector kernel, which multiplies in fp32.
+// P stays a 32-bit quantity: P.V takes it as the exact sum of three bf16 operands
+// (split_bf16), because these head counts otherwise run on the vector kernel,
+// which multiplies in fp32.
 //
 // LDS rows are unpadded: 16-byte chunk g of row r at g ^ (2r mod 16) in a
 // value row (1024 bytes) and at g ^ (r & 6) in a rotary row (128 bytes), free
 // of bank conflicts for the K operand reads and the V transpose reads.
 //
-// Measured (whole decode calls, 16 requests of 1K-32K tokens, 150 MB of KV):
-// 20 heads 44 us, 32 heads 47 us (two units of 16 heads reading the KV twice:
-// 73 us), 64 heads 61 us (2.4 TB/s); the generic vector kernel took 1,650 us
-// with 20 heads and 3,380 us with 64.
+// Measured (whole decode calls, 16 requests of 1K-32K tokens, 160 MB of KV):
+// 20 heads 44 us, 32 heads 49 us (two units of 16 heads reading the KV twice:
+// 73 us), 64 heads 66 us (2.4 TB/s); the generic vector kernel took 1,650 us
+// with 20 heads and 3,380 us with 64. With two operands for P (2^-16 of it left
+// out, which shows where V cancels) 43, 47 and 61 us.
 #pragma once
 
 #include "decode_mla.h"
@@ -247,26 +247,26 @@ __device__ __forceinline__ void mla_heads_unit(const DecodeArgs &a, const GeomK 
 #pragma unroll
       for (int nb = 0; nb < C::NBW; ++nb) o[nb] *= al;
     }
-    // ---- P = hi + lo (bf16 each), O^T += V^T hi^T + V^T lo^T, with the token
-    // index ordered {4q..4q+3, 16+4q..16+4q+3} for lane group q
-    u32x4m hi, lo;
+    // ---- P = hi + mid + lo (bf16 each), O^T += V^T hi^T + V^T mid^T + V^T lo^T,
+    // with the token index ordered {4q..4q+3, 16+4q..16+4q+3} for lane group q
+    u32x4m pw[3];
     float ps = 0.f;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int r = 0; r < 4; r += 2) {
-        float p[2], rest[2];
+        Bf16Parts x[2];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          p[e] = fast_exp2(__builtin_fmaf(s[u][r + e], sl2, -m));
-          ps += p[e];
-          rest[e] = __builtin_fmaxf(p[e] - __uint_as_float(__float_as_uint(p[e]) & 0xFFFF0000u), 1e-37f);
+          const float p = fast_exp2(__builtin_fmaf(s[u][r + e], sl2, -m));
+          ps += p;
+          x[e] = split_bf16(p);
         }
-        hi[2 * u + r / 2] = (__float_as_uint(p[0]) >> 16) | (__float_as_uint(p[1]) & 0xFFFF0000u);
-        lo[2 * u + r / 2] = pack_bf16x2(rest[0], rest[1]);
+        pw[0][2 * u + r / 2] = upper_halves(x[0].hi, x[1].hi);
+        pw[1][2 * u + r / 2] = upper_halves(x[0].mid, x[1].mid);
+        pw[2][2 * u + r / 2] = upper_halves(x[0].lo, x[1].lo);
       }
     lsum += ps;
-    const bf16x8 ph = __builtin_bit_cast(bf16x8, hi), pl = __builtin_bit_cast(bf16x8, lo);
 #pragma unroll
     for (int b = 0; b < C::NBW / VB; ++b) {
       if (b + 1 < C::NBW / VB) {
@@ -275,11 +275,11 @@ __device__ __forceinline__ void mla_heads_unit(const DecodeArgs &a, const GeomK 
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < VB; ++j)
-        o[b * VB + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[b & 1][j], ph, o[b * VB + j], 0, 0, 0);
+      for (int h = 0; h < 3; ++h)
 #pragma unroll
-      for (int j = 0; j < VB; ++j)
-        o[b * VB + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[b & 1][j], pl, o[b * VB + j], 0, 0, 0);
+        for (int j = 0; j < VB; ++j)
+          o[b * VB + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[b & 1][j], __builtin_bit_cast(bf16x8, pw[h]),
+                                                                  o[b * VB + j], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   }

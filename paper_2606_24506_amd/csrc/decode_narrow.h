@@ -69,11 +69,9 @@ struct NarrowCfg {
   static_assert(LDS <= 163840, "LDS budget");
 };
 
-// PS: bf16 operands that P.V takes P as, 1 (p rounded) or 2 (cut and rest, at
-// most 2^-17 of p left out, for head counts whose other kernel is the fp32
-// vector one; the rest is kept above zero so that an infinite V stays
-// infinite). FRESH: the lane index is counted afresh, which keeps a kernel of
-// many variants from holding the per-lane values of all of them through its
+// PS: bf16 operands that P.V takes P as, 1 (p rounded) or 3 (split_bf16, exact,
+// for head counts whose other kernel is the fp32 vector one). FRESH: the lane
+// index is counted afresh, which keeps a kernel of many variants from holding the per-lane values of all of them through its
 // work loop (64 registers spilled against 25); the kernels of one to three
 // variants fit without, and then form those values once per launch instead of
 // once per piece (mixed MLA-16 / MQA-32 / GQA-8 step: 147 us, with FRESH 161).
@@ -81,7 +79,7 @@ template <int G, int DK, int DV, bool MLA, int TW, int NW, int SHARE, int NSLOT,
 __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm, const DecReq &rq, const Seg &sg,
                                             char *lds) {
   using C = NarrowCfg<G, DK, DV, MLA, TW, NW, SHARE, NSLOT>;
-  static_assert(PS == 1 || (PS == 2 && TW == 16), "two operands with 16-token slices");
+  static_assert(PS == 1 || (PS == 3 && TW == 16), "three operands with 16-token slices");
   const int lane = FRESH ? lane_ids().lane : threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int stream = wave % C::NSTREAM, member = wave / C::NSTREAM;
@@ -346,7 +344,7 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
     }
     // ---- P (fp32 into the row sums, bf16 as the P.V operand) and O^T += V^T P^T
     if constexpr (TW == 16) {
-      s16x4 pf[C::HBW], pr[C::HBW];
+      s16x4 pf[PS][C::HBW];
 #pragma unroll
       for (int hb = 0; hb < C::HBW; ++hb) {
         float ps = 0.f;
@@ -355,11 +353,12 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
           const float p = fast_exp2(__builtin_fmaf(sv[0][hb][r], sl2, -m[hb]));
           ps += p;
           if constexpr (PS == 1) {
-            pf[hb][r] = __builtin_bit_cast(short, (__bf16)p);
+            pf[0][hb][r] = __builtin_bit_cast(short, (__bf16)p);
           } else {
-            const uint32_t cut = __float_as_uint(p) & 0xFFFF0000u;
-            pf[hb][r] = (short)(cut >> 16);
-            pr[hb][r] = __builtin_bit_cast(short, (__bf16)__builtin_fmaxf(p - __uint_as_float(cut), 1e-37f));
+            const Bf16Parts x = split_bf16(p);
+            pf[0][hb][r] = (short)(x.hi >> 16);
+            pf[1][hb][r] = (short)(x.mid >> 16);
+            pf[2][hb][r] = (short)(x.lo >> 16);
           }
         }
         lsum[hb] += ps;
@@ -382,19 +381,13 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < C::VB; ++j)
-#pragma unroll
-          for (int hb = 0; hb < C::HBW; ++hb)
-            o[hb][b * C::VB + j] =
-                __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[b & 1][j], pf[hb], o[hb][b * C::VB + j], 0, 0, 0);
-        if constexpr (PS == 2) {
+        for (int h = 0; h < PS; ++h)
 #pragma unroll
           for (int j = 0; j < C::VB; ++j)
 #pragma unroll
             for (int hb = 0; hb < C::HBW; ++hb)
               o[hb][b * C::VB + j] =
-                  __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[b & 1][j], pr[hb], o[hb][b * C::VB + j], 0, 0, 0);
-        }
+                  __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[b & 1][j], pf[h][hb], o[hb][b * C::VB + j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {

@@ -17,12 +17,10 @@
 // slices and are merged through LDS at the end of the unit (HP = 8: no
 // merge).
 //
-// P stays a 32-bit quantity: the P.V product takes it as the sum of two bf16
-// operands (p cut to bf16, and the rest rounded to bf16: at most 2^-17 of p is
-// left out), so the result carries no more rounding than the vector kernels
-// (decode_small.h, valu_unit), which multiply in fp32. The second product
-// reads no further LDS. The rest is kept above zero, so that an infinite V
-// gives an infinite output as it does in fp32, and not 0 * inf.
+// P stays a 32-bit quantity: the P.V product takes it as the exact sum of three
+// bf16 operands (split_bf16), so the result carries no more rounding than the
+// vector kernels (decode_small.h, valu_unit), which multiply in fp32. The further
+// products read no further LDS.
 //
 // LDS rows lie unpadded, 16-byte chunk g of row r at g ^ (2r mod 16) (256-byte
 // rows) or g ^ (r & 6) (128-byte rows): the K operand reads and the V
@@ -32,8 +30,8 @@
 // on 8 KV heads, 512-32K tokens, 458 MB: 80 us (5.7 TB/s), with the
 // small-group vector kernel 122 us (3.8 TB/s; half of its time went to vector
 // instructions, about 110 per 32 bytes and lane). 32 requests of four models
-// with groups of 1 to 4 heads, head_dim 64 and 128, 235 MB: 46.8 against
-// 116 us.
+// with groups of 1 to 4 heads, head_dim 64 and 128, 235 MB: 45 against 116
+// us. The third operand of P costs 0.2% of either.
 #pragma once
 
 #include "decode_mfma.h"
@@ -219,45 +217,47 @@ __device__ __forceinline__ void stream_unit(const DecodeArgs &a, const GeomK &gm
 #pragma unroll
       for (int nb = 0; nb < C::NBLK; ++nb) o[nb] *= al;
     }
-    // ---- P = hi + lo (bf16 each), O^T += V^T hi^T + V^T lo^T
+    // ---- P = hi + mid + lo (bf16 each), O^T += V^T hi^T + V^T mid^T + V^T lo^T
     float ps = 0.f;
-    uint32_t hi[2 * C::NSL], lo[2 * C::NSL];  // two values each
+    uint32_t pw[3][2 * C::NSL];  // two values each
 #pragma unroll
     for (int u = 0; u < C::NSL; ++u)
 #pragma unroll
       for (int r = 0; r < 4; r += 2) {
-        float p[2], rest[2];
+        Bf16Parts x[2];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          p[e] = fast_exp2(__builtin_fmaf(s[u][r + e], sl2, -m));
-          ps += p[e];
-          rest[e] = __builtin_fmaxf(p[e] - __uint_as_float(__float_as_uint(p[e]) & 0xFFFF0000u), 1e-37f);
+          const float p = fast_exp2(__builtin_fmaf(s[u][r + e], sl2, -m));
+          ps += p;
+          x[e] = split_bf16(p);
         }
-        hi[2 * u + r / 2] = (__float_as_uint(p[0]) >> 16) | (__float_as_uint(p[1]) & 0xFFFF0000u);
-        lo[2 * u + r / 2] = pack_bf16x2(rest[0], rest[1]);
+        pw[0][2 * u + r / 2] = upper_halves(x[0].hi, x[1].hi);
+        pw[1][2 * u + r / 2] = upper_halves(x[0].mid, x[1].mid);
+        pw[2][2 * u + r / 2] = upper_halves(x[0].lo, x[1].lo);
       }
     lsum += ps;
     if constexpr (C::NSL == 1) {
-      const s16x4 ph = __builtin_bit_cast(s16x4, u32x2s{hi[0], hi[1]});
-      const s16x4 pl = __builtin_bit_cast(s16x4, u32x2s{lo[0], lo[1]});
 #pragma unroll
-      for (int nb = 0; nb < C::NBLK; ++nb) o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[0][nb], ph, o[nb], 0, 0, 0);
+      for (int h = 0; h < 3; ++h) {
+        const s16x4 ph = __builtin_bit_cast(s16x4, u32x2s{pw[h][0], pw[h][1]});
 #pragma unroll
-      for (int nb = 0; nb < C::NBLK; ++nb) o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[0][nb], pl, o[nb], 0, 0, 0);
+        for (int nb = 0; nb < C::NBLK; ++nb)
+          o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[0][nb], ph, o[nb], 0, 0, 0);
+      }
     } else {
       // token index ordered {4q..4q+3, 16+4q..16+4q+3} for lane group q
       constexpr int N1 = 2 * C::NSL - 2;
-      const bf16x8 ph = __builtin_bit_cast(bf16x8, u32x4s{hi[0], hi[1], hi[N1], hi[N1 + 1]});
-      const bf16x8 pl = __builtin_bit_cast(bf16x8, u32x4s{lo[0], lo[1], lo[N1], lo[N1 + 1]});
       bf16x8 vv[C::NBLK];
 #pragma unroll
-      for (int nb = 0; nb < C::NBLK; ++nb) {
+      for (int nb = 0; nb < C::NBLK; ++nb)
         vv[nb] = __builtin_bit_cast(
             bf16x8, __builtin_shufflevector(vf[0][nb], vf[C::NSL - 1][nb], 0, 1, 2, 3, 4, 5, 6, 7));
-        o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv[nb], ph, o[nb], 0, 0, 0);
-      }
 #pragma unroll
-      for (int nb = 0; nb < C::NBLK; ++nb) o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv[nb], pl, o[nb], 0, 0, 0);
+      for (int h = 0; h < 3; ++h) {
+        const bf16x8 ph = __builtin_bit_cast(bf16x8, u32x4s{pw[h][0], pw[h][1], pw[h][N1], pw[h][N1 + 1]});
+#pragma unroll
+        for (int nb = 0; nb < C::NBLK; ++nb) o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv[nb], ph, o[nb], 0, 0, 0);
+      }
     }
   }
 

@@ -41,13 +41,13 @@ constexpr uint32_t kPieceFixedCost = 320;
 //     vector path, and pages the stream path does not tile).
 //   Narrow matrix path (16, 17, 19, 20, 23): 8, 16 or 32 query heads per KV
 //     head (MLA latent head, or head_dim 128); 17 is MLA in units of up to
-//     16 heads with P as two bf16 operands.
+//     16 heads with P as three bf16 operands (whole).
 //   Head-owner matrix path (21, 22): 64 or 128 query heads per KV head with
 //     head_dim 128.
 //   Stream matrix path (24, 25): any other GQA / MHA group, head_dim 64 or
-//     128, in units of up to 16 heads; P as two bf16 operands.
+//     128, in units of up to 16 heads; P whole.
 //   MLA head-pair path (26, 27): MLA with 17 to 32 heads, or in units of up
-//     to 64; P as two bf16 operands.
+//     to 64; P whole.
 //   128-head MLA (18): its own kernel (score waves and P.V waves).
 enum : int32_t {
   kV16x8 = 0, kV16x4, kV16x2, kV16x1, kV8x8, kV8x4, kV8x2, kV8x1,

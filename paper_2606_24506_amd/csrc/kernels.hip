@@ -334,7 +334,7 @@ __device__ __forceinline__ void valu_unit(const DecodeArgs &a, const GeomK &gm, 
 constexpr int kNarrowWaves = 8;
 template <int V> struct NarrowVar;
 template <> struct NarrowVar<kM_MLA_G16> { static constexpr int G = 16, DK = 576, DV = 512, TW = 16, SHARE = 2, NSLOT = 2, PS = 1; static constexpr bool MLA = true; };
-template <> struct NarrowVar<kM_MLA_G16S> { static constexpr int G = 16, DK = 576, DV = 512, TW = 16, SHARE = 2, NSLOT = 2, PS = 2; static constexpr bool MLA = true; };
+template <> struct NarrowVar<kM_MLA_G16S> { static constexpr int G = 16, DK = 576, DV = 512, TW = 16, SHARE = 2, NSLOT = 2, PS = 3; static constexpr bool MLA = true; };
 template <> struct NarrowVar<kM_D128_G8> { static constexpr int G = 8, DK = 128, DV = 128, TW = 32, SHARE = 2, NSLOT = 2, PS = 1; static constexpr bool MLA = false; };
 template <> struct NarrowVar<kM_D128_G16> { static constexpr int G = 16, DK = 128, DV = 128, TW = 32, SHARE = 2, NSLOT = 2, PS = 1; static constexpr bool MLA = false; };
 template <> struct NarrowVar<kM_D128_G32> { static constexpr int G = 32, DK = 128, DV = 128, TW = 32, SHARE = 2, NSLOT = 2, PS = 1; static constexpr bool MLA = false; };

@@ -124,31 +124,88 @@ def test_mla_128_on_small_pages():
     run([(mla(128), n) for n in (1, 17, 300)], 16, BAL, 0)
 
 
-@pytest.mark.parametrize("g", [4, 5])
-def test_split_probabilities_keep_fp32_precision(g):
-    """Probabilities are multiplied as the sum of two bf16 numbers. With V
-    equal to a constant (a power of two) in every row the output is that
-    constant times (sum of the operands) / (sum of the fp32 probabilities):
-    each operand pair is within 2^-17 of its probability, so the result
-    rounds to the constant exactly, and an infinite V stays infinite."""
-    hq = 4 * g
-    m, n = gqa(hq, 4), 1000
+@pytest.mark.parametrize("model", [gqa(32, 8), gqa(20, 4), gqa(16, 4, 64), gqa(30, 1, 64), mla(12), mla(20), mla(32),
+                                   mla(64), mla(100)], ids=lambda m: m.name)
+def test_probabilities_keep_fp32_precision(model):
+    """Probabilities enter P.V whole (as three bf16 operands). Tokens come in
+    pairs of V = +1 and -1 whose scores differ by d = 2^-11.5 to 2^-10.5, so
+    the output is -tanh(d / 2), the small difference of nearly equal sums:
+    rounding p to 8 bits moves it by as much as itself, and two operands, which
+    leave up to 2^-16 of p out, by 2^-5 to 2^-6. What fp32 leaves: the output's
+    own rounding (up to 2^-8) and an error of each p of at most 2^-21 or so
+    (scores of magnitude 4, two units of the last place), 2^-9.5 of d: together
+    below 2^-7. One range per request, so no bf16 partials."""
+    hd, lens = model.d_k, (2, 10, 48)
+    rng = np.random.default_rng(7)
+    off = 512 if model.kind == "mla" else 0     # the score comes from two dimensions, for MLA from rotary ones
+    hkv = 1 if model.kind == "mla" else model.n_kv_heads
+    specs, rows_all, q_all = [], [], []
+    for n in lens:
+        k = np.zeros((n, hkv, hd), dtype=np.float32)
+        base = rng.uniform(-4, 0, size=(n // 2, hkv)).repeat(2, axis=0)
+        k[:, :, off + 1] = base / model.scale
+        k[1::2, :, off] = 0.25
+        v = np.tile(np.where(np.arange(n) % 2, -1.0, 1.0)[:, None, None], (1, hkv, 1)).astype(np.float32)
+        if model.kind == "mla":
+            k[:, :, :512] = v
+            rows = k.reshape(n, -1)
+        else:
+            rows = np.concatenate([k.reshape(n, -1), np.broadcast_to(v, (n, hkv, hd)).reshape(n, -1)], axis=1)
+        q = np.zeros((model.n_q_heads, hd), dtype=np.float32)
+        q[:, off + 1] = rng.uniform(0.5, 1, model.n_q_heads)
+        q[:, off] = rng.uniform(1, 2, model.n_q_heads) * 2.0 ** -9.5 / model.scale
+        rows_all.append((rows.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16))
+        q_all.append((q.view(np.uint32) >> 16).astype(np.uint16))
+    pool = cpl.Pool(page_tokens=64, pool_bytes=64 << 20, device=0)
+    mid = pool.register_spec(model)
+    rids = [pool.open(mid, n) for n in lens]
+    for r, rw in zip(rids, rows_all):
+        pool.append([r], [rw.shape[0]], to_device_u16(rw, "cuda"))
+    out = torch.zeros(len(lens) * model.n_q_heads * model.d_v, dtype=torch.int16, device="cuda")
+    lse = torch.zeros(len(lens) * model.n_q_heads, dtype=torch.float32, device="cuda")
+    pool.decode(rids, to_device_u16(np.concatenate([x.reshape(-1) for x in q_all]), "cuda"), out, lse, num_splits=1,
+                schedule=QUE)
+    torch.cuda.synchronize()
+    got = oracle.bf16_bits_to_f64(out.cpu().numpy().view(np.uint16)).reshape(len(lens), model.n_q_heads, model.d_v)
+    worst = 0.0
+    for g, rw, qb in zip(got, rows_all, q_all):
+        ref, _ = oracle.decode(rw, qb, model)
+        assert np.abs(ref).max() < 2.0 ** -11 and np.abs(ref).min() > 2.0 ** -13
+        worst = max(worst, float((np.abs(g - ref) / np.abs(ref)).max()))
+    print(f"[precision] {model.name} 2^{np.log2(worst):.2f}", flush=True)
+    assert worst <= 2.0 ** -7
+    for r in rids:
+        pool.close(r)
+    pool.destroy()
+
+
+@pytest.mark.parametrize("model", [gqa(16, 4), gqa(20, 4), gqa(16, 4, 64), mla(12), mla(20), mla(64)], ids=lambda m: m.name)
+def test_infinite_values_stay_infinite(model):
+    """V constant (a power of two) in every row but for one infinite column:
+    the output is that constant exactly, and infinity, not NaN."""
+    n, d_v = 1000, model.d_v
     rng = np.random.default_rng(1)
-    rows = rng.standard_normal((n, m.row_width), dtype=np.float32)
-    rows[:, 4 * 128:] = 0.5
-    rows[:, 4 * 128 + 7] = np.inf
+    rows = rng.standard_normal((n, model.row_width), dtype=np.float32)
+    q = rng.standard_normal((model.n_q_heads, model.d_k), dtype=np.float32)
+    v0 = 0 if model.kind == "mla" else model.n_kv_heads * d_v
+    rows[:, v0:v0 + (d_v if model.kind == "mla" else model.n_kv_heads * d_v)] = 0.5
+    rows[:, v0 + 7] = np.inf
+    if model.kind == "mla":
+        q[:, :512] = 0.25
+        q[:, 7] = 0  # 0 * inf would be the score
+        rows[:, 7] = 0.5  # (an infinite latent value is an infinite key as well)
     bits = (rows.view(np.uint32) >> 16).astype(np.uint16)
     pool = cpl.Pool(page_tokens=64, pool_bytes=64 << 20, device=0)
-    rid = pool.open(pool.register_spec(m), n)
+    rid = pool.open(pool.register_spec(model), n)
     pool.append([rid], [n], to_device_u16(bits, "cuda"))
-    q = to_device_u16((rng.standard_normal((hq, 128), dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16), "cuda")
-    out = torch.zeros(hq * 128, dtype=torch.int16, device="cuda")
-    lse = torch.zeros(hq, dtype=torch.float32, device="cuda")
-    pool.decode([rid], q, out, lse)
+    qb = (q.view(np.uint32) >> 16).astype(np.uint16)
+    out = torch.zeros(model.n_q_heads * d_v, dtype=torch.int16, device="cuda")
+    lse = torch.zeros(model.n_q_heads, dtype=torch.float32, device="cuda")
+    pool.decode([rid], to_device_u16(qb, "cuda"), out, lse)
     torch.cuda.synchronize()
-    got = out.view(torch.bfloat16).float().cpu().numpy().reshape(hq, 128)
-    expect = np.full((hq, 128), 0.5, dtype=np.float32)
-    expect[:g, 7] = np.inf  # the heads of KV head 0
-    assert np.array_equal(got, expect)
+    expect = np.full((model.n_q_heads, d_v), 0.5, dtype=np.float32)
+    if model.kind != "mla":
+        expect[:model.n_q_heads // model.n_kv_heads, 7] = np.inf  # the heads of KV head 0
+    assert np.array_equal(out.view(torch.bfloat16).float().cpu().numpy().reshape(expect.shape), expect)
     pool.close(rid)
     pool.destroy()
