@@ -969,13 +969,20 @@ cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const vo
 
 // Time per KiB of KV, in eighths of what the narrow and stream kernels take:
 // the kernels of more heads per KV byte run below HBM speed, and where they
-// share a launch by bytes their workgroups end last. Swept on launches of
-// these models (24 requests of MLA-20, MLA-64, GQA-28:4 and GQA-40:8): 50.0 us a
-// call with 8 for each, 41.5 with 10 and 14, 38.5 with 12 and 18, 40.7 with 16 and 24;
-// MQA-128 with GQA-128:2: 48.2 with 8 and 8, 47.3 with 10 and 8, 52.2 with 8 and 12.
+// share a launch by bytes their workgroups end last. us a call of 24 to 40
+// requests, by bytes (8) and with these weights:
+//   MLA to 32 heads 11, to 64 heads 18: MLA-20, MLA-64, GQA-28:4 and GQA-40:8
+//   54.3, 40.7; MLA-64 with GQA-32:8 92.8, 65.7; with MLA-16 59.1, 55.2; MLA-32
+//   with MQA-16 and GQA-64:8 92.5, 90.0; with MLA-16 61.0, 58.3; MLA-20 with MQA-32
+//   43.4, 43.3 (45.6 with 12; with 10 the first batch's larger form loses 5%).
+//   128 heads with separate K and V 10: MQA-128 with GQA-24:8 67.6, 59.3; with
+//   GQA-32:4 72.4, 67.1; with 64 heads 35.7, 33.7; but with MQA-32 54.0, 55.4 and
+//   with MLA-16 41.2, 42.3 (9 halves the losses and loses 5% on MQA-128 with
+//   GQA-128:2). 64 heads stay at 8: 10 gains 8% beside GQA-24:8 and loses 4% beside
+//   MQA-32.
 int32_t time_weight(int32_t variant) {
   switch (variant) {
-    case kM_MLA_H32: return 12;
+    case kM_MLA_H32: return 11;
     case kM_MLA_H64: return 18;
     case kM_D128_G128: return 10;
     default: return kTimeWeightUnit;

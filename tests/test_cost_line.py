@@ -27,7 +27,7 @@ class Model:
 
 # kinds of models with the steps and weights of their kernels
 MLA16 = Model(1152, 64, out=16 * 512)
-MLA20 = Model(1152, 64, 12, 20 * 512)
+MLA20 = Model(1152, 64, 11, 20 * 512)
 MLA64 = Model(1152, 32, 18, 64 * 512)
 MLA200 = Model(1152, 32, 18, 200 * 512, 4)
 MQA32 = Model(512, 128, out=32 * 128)
