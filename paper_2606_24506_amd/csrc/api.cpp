@@ -658,7 +658,7 @@ cp_status launch_appends(cp_pool *p, const std::vector<AppItem> &items, const vo
           std::copy_n(p->st.pte_mirror() + it.ent, it.n_ent, a.ent + a.n_ent);
           a.n_ent += (int32_t)it.n_ent;
         }
-        const uint32_t R = copy_rows_per_block((uint32_t)a.geom[mi].row_elems, (uint32_t)P);
+        const uint32_t R = copy_rows_per_block((uint32_t)a.geom[mi].row_elems);
         blocks += (it.n_new + R - 1) / R;
       }
       ++i;

@@ -163,14 +163,16 @@ struct MergeArgs {
 };
 
 // Append and gather: a workgroup of kCopyThreads copies up to kCopyUnroll
-// 16-byte segments per thread, and so this many rows (a power of two where the
-// page allows it, so that a workgroup seldom meets two pages).
+// 16-byte segments per thread, and so this many rows (a power of two, so that a
+// workgroup seldom meets two pages of a power of two of tokens). At least 10 KiB,
+// whatever the page holds: a launch has less than 2^32 threads, and 2^24
+// workgroups of a row of 256 bytes each would bound a call to 4 GiB.
 constexpr int kCopyThreads = 256, kCopyUnroll = 5;
-constexpr uint32_t copy_rows_per_block(uint32_t row_elems, uint32_t page_tokens) {
+constexpr uint32_t copy_rows_per_block(uint32_t row_elems) {
   const uint32_t fit = (uint32_t)(kCopyThreads * kCopyUnroll) / (row_elems / 8);
   uint32_t r = 1;
   while (2 * r <= fit) r *= 2;
-  return r < page_tokens ? r : page_tokens;
+  return r;
 }
 
 struct AppReq {

@@ -35,7 +35,11 @@ namespace cp {
 // few. Rows of one page are one contiguous block in an MLA page; in a GQA
 // page each KV head's part of a row is one segment of d elements. Gathering
 // 53K tokens of six requests (112 MB read and written), a launch each: 31.7 us,
-// with a workgroup per row 39.3; the largest, 67 MB, moves 5.8 TB/s.
+// with a workgroup per row 39.3; the largest, 67 MB, moves 5.8 TB/s. The gather
+// reads pages past the caches: with eight such batches in turn, so that rows come
+// from HBM, 33.0 us a call, with plain loads 36.3, with a workgroup per row 41.1.
+// (One batch over and over, rows from the Infinity Cache: 30.7, 28.1 and 33.1; a
+// single request of 67 MB over and over 22.6, 20.6 and 19.6.)
 typedef unsigned int u32x4c __attribute__((ext_vector_type(4)));
 
 template <bool TO_PAGE>
@@ -68,6 +72,25 @@ CP_DEV void copy_rows(const GeomK &g, uint8_t *page, uint32_t slot0, uint32_t nr
   }
 }
 
+// The same for rows of pages that hold less than a workgroup's rows: row i is
+// token pos0 + i of the plane, and every segment looks its page up (pte_of). One
+// page after another is a chain of page-table loads: a gather of 15K rows of 512
+// bytes on pages of one token 23.1 us a call, this way 15.7.
+template <bool TO_PAGE, class F>
+CP_DEV void copy_rows_small_pages(const GeomK &g, uint8_t *pool, uint32_t pos0, uint32_t nrows, uint16_t *flat,
+                                  F &&pte_of) {
+  const uint32_t nseg = (uint32_t)g.row_elems / 8, total = nrows * nseg, P = (uint32_t)g.page_tokens;
+  for (uint32_t i = threadIdx.x; i < total; i += kCopyThreads) {
+    const uint32_t row = i / nseg, pos = pos0 + row, pg = pos / P;
+    uint8_t *const at = pool + ((uint64_t)pte_of(pg) << 8) + row_seg_offset(g, pos - pg * P, i - row * nseg);
+    u32x4c *const f = reinterpret_cast<u32x4c *>(flat) + i;
+    if (TO_PAGE)
+      *reinterpret_cast<u32x4c *>(at) = *f;
+    else
+      *f = *reinterpret_cast<const u32x4c *>(at);
+  }
+}
+
 // Rows [block R, block R + R) of one item. Entries of the item's new pages
 // come from the launch arguments; the workgroup that holds such a page's
 // first row writes its page-table entry.
@@ -75,21 +98,26 @@ __global__ __launch_bounds__(kCopyThreads) void kv_append_kernel(const AppendArg
   const int r = sorted_search(a.n_req, blockIdx.x, [&](int i) { return a.req[i].block_begin; });
   const AppReq &rq = a.req[r];
   const GeomK &g = a.geom[rq.model];
-  const uint32_t P = (uint32_t)g.page_tokens, R = copy_rows_per_block((uint32_t)g.row_elems, P);
+  const uint32_t P = (uint32_t)g.page_tokens, R = copy_rows_per_block((uint32_t)g.row_elems);
   const uint32_t row0 = (blockIdx.x - rq.block_begin) * R, row1 = min(rq.n_new, row0 + R);
   const uint32_t first_new = (rq.old_len + P - 1) / P;  // first page the item opens
+  if (rq.ent != kNoEnt) {
+    const uint32_t pg = (rq.old_len + row0 + P - 1) / P + threadIdx.x;  // at most R of them start here
+    if (pg <= (rq.old_len + row1 - 1) / P) a.pte[rq.pte_base + pg] = a.ent[rq.ent + (pg - first_new)];
+  }
+  auto pte_of = [&](uint32_t pg) {
+    return rq.ent != kNoEnt && pg >= first_new ? a.ent[rq.ent + (pg - first_new)] : a.pte[rq.pte_base + pg];
+  };
+  uint16_t *const src = const_cast<uint16_t *>(a.rows) + rq.src_off;
+  if (P < R) {
+    copy_rows_small_pages<true>(g, a.pool, rq.old_len + row0, row1 - row0, src + (uint64_t)row0 * (uint32_t)g.row_elems,
+                                pte_of);
+    return;
+  }
   for (uint32_t row = row0; row < row1;) {
     const uint32_t pos = rq.old_len + row, pg = pos / P, slot = pos - pg * P;
     const uint32_t n = min(row1 - row, P - slot);
-    uint32_t pte;
-    if (rq.ent != kNoEnt && pg >= first_new) {
-      pte = a.ent[rq.ent + (pg - first_new)];
-      if (slot == 0 && threadIdx.x == 0) a.pte[rq.pte_base + pg] = pte;
-    } else {
-      pte = a.pte[rq.pte_base + pg];
-    }
-    copy_rows<true>(g, a.pool + ((uint64_t)pte << 8), slot, n,
-                    const_cast<uint16_t *>(a.rows) + rq.src_off + (uint64_t)row * (uint32_t)g.row_elems);
+    copy_rows<true>(g, a.pool + ((uint64_t)pte_of(pg) << 8), slot, n, src + (uint64_t)row * (uint32_t)g.row_elems);
     row += n;
   }
 }
@@ -117,14 +145,20 @@ hipError_t launch_stack_push(const StackPushArgs &a, hipStream_t stream) {
 // Rows [start + block R, ...) of KV plane blockIdx.y.
 __global__ __launch_bounds__(kCopyThreads) void kv_gather_kernel(const GatherArgs a) {
   const GeomK &g = a.geom;
-  const uint32_t P = (uint32_t)g.page_tokens, R = copy_rows_per_block((uint32_t)g.row_elems, P);
+  const uint32_t P = (uint32_t)g.page_tokens, R = copy_rows_per_block((uint32_t)g.row_elems);
   const uint32_t row0 = blockIdx.x * R, row1 = min(a.n_tok, row0 + R);
   const uint32_t pte_base = a.pte_base + blockIdx.y * a.plane;
   uint16_t *const dst = a.dst + (uint64_t)blockIdx.y * a.n_tok * (uint32_t)g.row_elems;
+  uint8_t *const pool = const_cast<uint8_t *>(a.pool);
+  if (P < R) {
+    copy_rows_small_pages<false>(g, pool, a.start + row0, row1 - row0, dst + (uint64_t)row0 * (uint32_t)g.row_elems,
+                                 [&](uint32_t pg) { return a.pte[pte_base + pg]; });
+    return;
+  }
   for (uint32_t row = row0; row < row1;) {
     const uint32_t pos = a.start + row, pg = pos / P, slot = pos - pg * P;
     const uint32_t n = min(row1 - row, P - slot);
-    copy_rows<false>(g, const_cast<uint8_t *>(a.pool) + ((uint64_t)a.pte[pte_base + pg] << 8), slot, n,
+    copy_rows<false>(g, pool + ((uint64_t)a.pte[pte_base + pg] << 8), slot, n,
                      dst + (uint64_t)row * (uint32_t)g.row_elems);
     row += n;
   }
@@ -132,7 +166,7 @@ __global__ __launch_bounds__(kCopyThreads) void kv_gather_kernel(const GatherArg
 
 hipError_t launch_gather(const GatherArgs &a, hipStream_t stream) {
   if (a.n_tok == 0) return hipSuccess;
-  const uint32_t R = copy_rows_per_block((uint32_t)a.geom.row_elems, (uint32_t)a.geom.page_tokens);
+  const uint32_t R = copy_rows_per_block((uint32_t)a.geom.row_elems);
   hipLaunchKernelGGL(kv_gather_kernel, dim3((a.n_tok + R - 1) / R, a.geom.layers), dim3(kCopyThreads), 0, stream, a);
   return hipGetLastError();
 }
