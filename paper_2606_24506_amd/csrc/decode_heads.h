@@ -310,7 +310,8 @@ __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm,
 #pragma unroll
     for (int s2 = 0; s2 < C::NSTREAM; ++s2) {
       const float ms = m_x[s2 * G + wh];
-      L += ms == -INFINITY ? 0.f : l_x[s2 * G + wh] * fast_exp2(ms - Mw);
+      const float l = l_x[s2 * G + wh];
+      L += ms == -INFINITY ? (l != l ? l : 0.f) : l * fast_exp2(ms - Mw);  // (all-NaN scores leave m = -inf)
     }
     const float inv = 1.0f / L;
     const uint32_t head = (uint32_t)(kvh * G + wh);

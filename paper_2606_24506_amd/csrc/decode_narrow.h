@@ -517,7 +517,8 @@ __device__ __forceinline__ void narrow_unit(const DecodeArgs &a, const GeomK &gm
 #pragma unroll
     for (int s2 = 0; s2 < C::NSTREAM; ++s2) {
       const float ms = m_x[s2 * C::HEADS + hh];
-      L += ms == -INFINITY ? 0.f : l_x[s2 * C::HEADS + hh] * fast_exp2(ms - M);
+      const float l = l_x[s2 * C::HEADS + hh];
+      L += ms == -INFINITY ? (l != l ? l : 0.f) : l * fast_exp2(ms - M);  // (all-NaN scores leave m = -inf)
     }
     const float inv = 1.0f / L;
 #pragma unroll 1

@@ -209,3 +209,29 @@ def test_infinite_values_stay_infinite(model):
     assert np.array_equal(out.view(torch.bfloat16).float().cpu().numpy().reshape(expect.shape), expect)
     pool.close(rid)
     pool.destroy()
+
+
+@pytest.mark.parametrize("model", [gqa(64, 1), gqa(128, 1), gqa(32, 8), gqa(28, 1), gqa(16, 4, 64), mla(12), mla(20),
+                                   mla(64)], ids=lambda m: m.name)
+def test_nan_keys_reach_output_and_lse(model):
+    """Keys of NaN in one 32-token tile (one stream has nothing else): the
+    heads that read them have NaN outputs and a NaN lse."""
+    n = 64
+    rng = np.random.default_rng(2)
+    rows = rng.standard_normal((n, model.row_width), dtype=np.float32)
+    rows[32:, 512 if model.kind == "mla" else 0] = np.nan  # a rotary element, or one of KV head 0's keys
+    q = rng.standard_normal((model.n_q_heads, model.d_k), dtype=np.float32)
+    pool = cpl.Pool(page_tokens=64, pool_bytes=64 << 20, device=0)
+    rid = pool.open(pool.register_spec(model), n)
+    pool.append([rid], [n], to_device_u16((rows.view(np.uint32) >> 16).astype(np.uint16), "cuda"))
+    out = torch.zeros(model.n_q_heads * model.d_v, dtype=torch.int16, device="cuda")
+    lse = torch.zeros(model.n_q_heads, dtype=torch.float32, device="cuda")
+    pool.decode([rid], to_device_u16((q.view(np.uint32) >> 16).astype(np.uint16), "cuda"), out, lse, num_splits=1,
+                schedule=QUE)
+    torch.cuda.synchronize()
+    hit = torch.arange(model.n_q_heads) < model.n_q_heads // (1 if model.kind == "mla" else model.n_kv_heads)
+    got = out.view(torch.bfloat16).float().cpu().view(model.n_q_heads, model.d_v)
+    assert torch.isnan(got[hit]).all() and torch.isfinite(got[~hit]).all()
+    assert torch.isnan(lse.cpu()[hit]).all() and torch.isfinite(lse.cpu()[~hit]).all()
+    pool.close(rid)
+    pool.destroy()
