@@ -1,10 +1,10 @@
-"""Register budgets of the decode kernels the benchmark batches run, read
+"""Register budgets of the matrix-core decode kernels, read
 from the compiler's kernel metadata and assembly (a device-only compile
 with the library's own flags; CPU only). The narrow kernel of the mixed
 batch sits a few registers under its 256-register budget: changes that push
 it over spill inside the streaming loop and cost a third of its speed. The
-128-head MLA kernel may spill a few registers at piece level, but none
-inside its two tile loops: a scratch reload there comes with a wait for
+128-head MLA kernel and the kernel of every matrix variant may spill a few
+registers at piece level, but none inside their tile loops: a scratch reload there comes with a wait for
 every load in flight, tile loads included. These are checked here rather
 than found on the GPU."""
 import os
@@ -31,15 +31,34 @@ BUDGET = {
 }
 
 
+def mask_kernel(*variants):
+    """The kernel of a set of variants (kargs.h)."""
+    return f"_ZN2cp13decode_kernelILj{sum(1 << v for v in variants)}EEEvNS_10DecodeArgsE"
+
+
+HEADS, STREAM, PAIRS, NARROW = (21, 22), (24, 25), (26, 27), (16, 17, 19, 20, 23)
+# padded MLA-16 with P whole, the head-owner, stream and MLA head-pair kernels,
+# alone, by family and together
+BUDGET.update({mask_kernel(*v): 0 for v in [(17,), (21,), (22,), HEADS, (24,), (25,), STREAM, (26,), (27,), PAIRS,
+                                            HEADS + STREAM + PAIRS]})
+ALL_MATRIX = mask_kernel(*NARROW, *HEADS, *STREAM, *PAIRS)
+BUDGET[ALL_MATRIX] = 20
+
 MLA_KERNEL = "_ZN2cp17decode_mla_kernelENS_10DecodeArgsE"
 
 
+ASM = {}  # source -> its assembly, compiled once
+
+
 def compile_asm(src, tmp_path):
+    if src in ASM:
+        return ASM[src]
     out = tmp_path / (src + ".s")
     cmd = [build.HIPCC, *build.DEVICE_FLAGS, *build.KERNEL_FLAGS, *build.COMMON, "--cuda-device-only", "-S",
            os.path.join(build.CSRC, src), "-o", str(out)]
     subprocess.run(cmd, check=True, capture_output=True, text=True)
-    return out.read_text()
+    ASM[src] = out.read_text()
+    return ASM[src]
 
 
 def kernel_metadata(src, tmp_path):
@@ -83,5 +102,15 @@ def test_mla_tile_loops_do_not_touch_scratch(tmp_path):
     # the score waves' loop and the P.V waves' loop
     assert len(loops) == 2, len(loops)
     for body in loops:
+        scratch = [l.strip() for l in body if "scratch_" in l]
+        assert not scratch, scratch[:4]
+
+
+@pytest.mark.parametrize("kernel,loops", [(ALL_MATRIX, 11), (mask_kernel(*HEADS, *STREAM, *PAIRS), 6)])
+def test_shared_kernels_do_not_touch_scratch_in_their_loops(kernel, loops, tmp_path):
+    """One loop per variant."""
+    bodies = tile_loops(compile_asm("kernels.hip", tmp_path), kernel)
+    assert len(bodies) == loops
+    for body in bodies:
         scratch = [l.strip() for l in body if "scratch_" in l]
         assert not scratch, scratch[:4]
