@@ -127,7 +127,8 @@ typedef struct {
   /* Cap on the device memory the pool may hold for split-KV partial
    * results (the per-range outputs and lse values a long request's decode
    * merges); 0 means no cap. A decode whose split plan needs more fails
-   * with CP_ENOMEM before anything is enqueued or any state changes; the
+   * with CP_ENOMEM before anything is enqueued or any state changes (the
+   * balanced schedule first gives up ranges finer than pages); the
    * queue and grid schedules with num_splits = 1 need none. */
   uint64_t max_workspace_bytes;
   /* 0: cp_attn_decode_step allocates a new token's pages on the host and
@@ -272,7 +273,8 @@ cp_status cp_request_pages(cp_pool *pool, int32_t req_id, int64_t first, int64_t
  * req_ids, n_new: host arrays of n entries; req_ids must be distinct;
  *   n_new[i] >= 0.
  * New pages come from the model's slab, or a fresh chunk of the shared
- *   budget; their page-table entries are written before the copy runs.
+ *   budget; their page-table entries are written by the copy's launch, or
+ *   (more than 352 of them) by a copy ahead of it.
  * Errors: CP_EINVAL (unknown or duplicate id, negative count, growth past
  *   the reservation, rows == NULL on a device pool), CP_EHIP. */
 cp_status cp_kv_append(cp_pool *pool, int32_t n, const int32_t *req_ids, const int32_t *n_new,
@@ -309,14 +311,19 @@ typedef enum {
    * others: of 16), and in fp32 precision for every other geometry. */
   CP_PATH_AUTO = 0,
   CP_PATH_VALU = 1, /* force the vector (wavefront-reduction) kernel for every model */
-  CP_PATH_MFMA = 2  /* force the matrix-core kernel for every model */
+  /* Force the matrix-core kernels; only for MLA with 16, 32 or 128 heads and
+   * for groups of 8, 16, 32, 64 or 128 query heads per KV head of width 128
+   * (pages as above). A call with any other model is refused (CP_EINVAL), also
+   * where the automatic path runs that model on the matrix cores. */
+  CP_PATH_MFMA = 2
 } cp_path;
 
 typedef enum {
-  /* Persistent grid, one workgroup per CU slot; the launch's pages, in
-   * request order, are cut into equal-cost contiguous ranges, one per
-   * workgroup, so ragged contexts and mixed models balance to within one
-   * page. A request spanning several ranges is merged afterwards. */
+  /* Persistent grid, one workgroup per CU slot; the launch's KV, in request
+   * order, is cut into equal-cost contiguous ranges, one per workgroup, so
+   * ragged contexts and mixed models balance to within one page, or less:
+   * ranges may end inside pages of more than 128 KiB. A request spanning
+   * several ranges is merged afterwards. */
   CP_SCHED_BALANCED = 0,
   /* Persistent grid whose workgroups pull (request, KV range) units from a
    * device queue, costliest first. */
@@ -359,7 +366,8 @@ cp_status cp_attn_decode_ex(cp_pool *pool, int32_t n, const int32_t *req_ids, co
  * and no other device allocation. The caller still passes q, out and lse.
  * A plan needing more than that (partial outputs: 2 * n_q_heads * d_v bytes
  * per KV range of each split request, plus 4 * n_q_heads for lse) fails
- * with CP_EINVAL before anything is enqueued; the DeepSeek-V3-shaped batch
+ * with CP_EINVAL before anything is enqueued (every decode call gives up
+ * ranges finer than pages where they would not fit); the DeepSeek-V3-shaped batch
  * (8 x 128K tokens, 128 heads) and the 512K-token burst need about 35 MB.
  * The array is shared by every call on one GPU, whichever pool it is on,
  * and keeps the last call's contents (nothing in it needs clearing):

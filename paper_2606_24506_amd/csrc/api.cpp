@@ -960,7 +960,8 @@ cp_status decode_prepare(cp_pool *p, int32_t n, const int32_t *req_ids, const vo
   for (int32_t i = 0; i < n; ++i) {
     const int32_t m = p->st.req(req_ids[i]).model;
     if (o.path == CP_PATH_MFMA && matrix_variant(p->st.model(m), P) < 0)
-      return fail(CP_EINVAL, "model %d has no matrix-core variant (needs a group of 8, 16, 32, 64 or 128 query heads per KV head)", m);
+      return fail(CP_EINVAL, "model %d has no matrix-core variant that the forced path takes (MLA with 16, 32 or 128 heads, or head_dim "
+                  "128 with 8, 16, 32, 64 or 128 query heads per KV head)", m);
   }
   *o_out = o;
   *gk_out = std::move(gk);

@@ -1,4 +1,4 @@
-// Matrix-core decode path for 33 to 128 query heads per KV head with separate
+// Matrix-core decode path for 64 or 128 query heads per KV head with separate
 // K and V rows (MQA / GQA groups, head_dim 128). Per KV byte there are 64 to
 // 128 flops, a quarter to a half of what the matrix cores deliver at HBM
 // speed, so the kernel must keep both busy: what it avoids is any exchange
@@ -163,7 +163,7 @@ __device__ __forceinline__ void heads_unit(const DecodeArgs &a, const GeomK &gm,
     if (i + C::NSLOT - 2 < mine) issue(i + C::NSLOT - 2);
     if (i + C::NSLOT - 1 < mine) issue(i + C::NSLOT - 1);
     if (i >= mine) continue;
-    // tokens of the two tiles; the second is absent (negative) at an odd end
+    // tokens of the two tiles; the second is absent (0) at an odd end
     int valid[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) valid[k] = i + k < mine ? min(T, (int)(tok_end - tok_begin) - (first + step * (i + k)) * T) : 0;

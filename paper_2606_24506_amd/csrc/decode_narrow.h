@@ -72,7 +72,7 @@ struct NarrowCfg {
 // PS: bf16 operands that P.V takes P as, 1 (p rounded) or 3 (split_bf16, exact,
 // for head counts whose other kernel is the fp32 vector one). FRESH: the lane
 // index is counted afresh, which keeps a kernel of many variants from holding the per-lane values of all of them through its
-// work loop (64 registers spilled against 25); the kernels of one to three
+// work loop (60 registers spilled against 17); the kernels of one to three
 // variants fit without, and then form those values once per launch instead of
 // once per piece (mixed MLA-16 / MQA-32 / GQA-8 step: 147 us, with FRESH 161).
 template <int G, int DK, int DV, bool MLA, int TW, int NW, int SHARE, int NSLOT, int PS, bool FRESH>

@@ -136,7 +136,7 @@ struct DecodeArgs {
   uint32_t *entry_done;
   int32_t n_req, n_units;
   int32_t schedule;     // kSchedBalanced, kSchedQueue or kSchedGrid
-  uint32_t total_cost;  // balanced: summed page costs of the launch
+  uint32_t total_cost;  // balanced: length of the launch's cost line
   GeomK geom[kMaxLaunchModels];
   DecReq req[kMaxReqPerLaunch];
   uint32_t ent_tag[kMaxReqPerLaunch];
