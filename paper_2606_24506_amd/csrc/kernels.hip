@@ -94,6 +94,9 @@ CP_DEV void copy_rows_small_pages(const GeomK &g, uint8_t *pool, uint32_t pos0, 
 // Rows [block R, block R + R) of one item. Entries of the item's new pages
 // come from the launch arguments; the workgroup that holds such a page's
 // first row writes its page-table entry.
+// SMALL: some model's pages hold less than a workgroup's rows (kernels of their
+// own: the branch costs the others 1%).
+template <bool SMALL>
 __global__ __launch_bounds__(kCopyThreads) void kv_append_kernel(const AppendArgs a) {
   const int r = sorted_search(a.n_req, blockIdx.x, [&](int i) { return a.req[i].block_begin; });
   const AppReq &rq = a.req[r];
@@ -109,7 +112,7 @@ __global__ __launch_bounds__(kCopyThreads) void kv_append_kernel(const AppendArg
     return rq.ent != kNoEnt && pg >= first_new ? a.ent[rq.ent + (pg - first_new)] : a.pte[rq.pte_base + pg];
   };
   uint16_t *const src = const_cast<uint16_t *>(a.rows) + rq.src_off;
-  if (P < R) {
+  if (SMALL && P < R) {
     copy_rows_small_pages<true>(g, a.pool, rq.old_len + row0, row1 - row0, src + (uint64_t)row0 * (uint32_t)g.row_elems,
                                 pte_of);
     return;
@@ -124,7 +127,13 @@ __global__ __launch_bounds__(kCopyThreads) void kv_append_kernel(const AppendArg
 
 hipError_t launch_append(const AppendArgs &a, hipStream_t stream) {
   if (a.n_blocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(kv_append_kernel, dim3(a.n_blocks), dim3(kCopyThreads), 0, stream, a);
+  bool small = false;
+  for (int m = 0; m < kMaxLaunchModels && a.geom[m].row_elems; ++m)
+    small = small || (uint32_t)a.geom[m].page_tokens < copy_rows_per_block((uint32_t)a.geom[m].row_elems);
+  if (small)
+    hipLaunchKernelGGL(kv_append_kernel<true>, dim3(a.n_blocks), dim3(kCopyThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL(kv_append_kernel<false>, dim3(a.n_blocks), dim3(kCopyThreads), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -143,6 +152,7 @@ hipError_t launch_stack_push(const StackPushArgs &a, hipStream_t stream) {
 // ------------------------------------------------------------- gather
 
 // Rows [start + block R, ...) of KV plane blockIdx.y.
+template <bool SMALL>
 __global__ __launch_bounds__(kCopyThreads) void kv_gather_kernel(const GatherArgs a) {
   const GeomK &g = a.geom;
   const uint32_t P = (uint32_t)g.page_tokens, R = copy_rows_per_block((uint32_t)g.row_elems);
@@ -150,7 +160,7 @@ __global__ __launch_bounds__(kCopyThreads) void kv_gather_kernel(const GatherArg
   const uint32_t pte_base = a.pte_base + blockIdx.y * a.plane;
   uint16_t *const dst = a.dst + (uint64_t)blockIdx.y * a.n_tok * (uint32_t)g.row_elems;
   uint8_t *const pool = const_cast<uint8_t *>(a.pool);
-  if (P < R) {
+  if (SMALL) {
     copy_rows_small_pages<false>(g, pool, a.start + row0, row1 - row0, dst + (uint64_t)row0 * (uint32_t)g.row_elems,
                                  [&](uint32_t pg) { return a.pte[pte_base + pg]; });
     return;
@@ -167,7 +177,11 @@ __global__ __launch_bounds__(kCopyThreads) void kv_gather_kernel(const GatherArg
 hipError_t launch_gather(const GatherArgs &a, hipStream_t stream) {
   if (a.n_tok == 0) return hipSuccess;
   const uint32_t R = copy_rows_per_block((uint32_t)a.geom.row_elems);
-  hipLaunchKernelGGL(kv_gather_kernel, dim3((a.n_tok + R - 1) / R, a.geom.layers), dim3(kCopyThreads), 0, stream, a);
+  const dim3 grid((a.n_tok + R - 1) / R, a.geom.layers);
+  if ((uint32_t)a.geom.page_tokens < R)
+    hipLaunchKernelGGL(kv_gather_kernel<true>, grid, dim3(kCopyThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL(kv_gather_kernel<false>, grid, dim3(kCopyThreads), 0, stream, a);
   return hipGetLastError();
 }
 
