@@ -186,3 +186,38 @@ def test_half_pages_are_not_cut_for_nothing(shim):
     for lens in ([18000 // 16] * 16, [28000 // 16] * 16, [1100] * 16, [140 * k for k in range(1, 18)]):
         reqs = [(MLA16, t) for t in lens]
         assert plan(shim, reqs, 128) == plan(shim, reqs, 128, whole=True)
+
+
+def kernel_of(spec):
+    """A model spec as the plan sees it, with the step and weight of its kernel."""
+    if spec.kind == "mla":
+        step, weight, blocks = (64, 8, 1) if spec.n_q_heads <= 16 else (64, 11, 1) if spec.n_q_heads <= 32 else (32, 18, 64)
+        rereads = -(-spec.n_q_heads // blocks) if blocks > 1 else 1
+        return Model(1152, step, weight, spec.n_q_heads * 512, rereads)
+    hkv, g, d = spec.n_kv_heads, spec.n_q_heads // spec.n_kv_heads, spec.head_dim
+    rereads, weight = 1, 8
+    if d == 128 and g in (8, 16, 32):
+        step = 32 if hkv % 4 == 0 else 128
+    elif d == 128 and g in (64, 128):
+        step, weight = (32, 10) if g == 128 else (32 if hkv % 2 == 0 else 64, 8)
+    else:
+        step, rereads = (16 if d == 128 else 32) * 8 // min(8, hkv & -hkv), -(-g // 16)
+    return Model(4 * hkv * d, step, weight, spec.n_q_heads * d, rereads)
+
+
+def test_gpu_batches_have_finer_ranges(shim):
+    """The batches by which the GPU tests mean to reach ranges inside pages, and
+    launches shared by time, do so."""
+    from test_gpu_subpage_ranges import BY_TIME, CUT, cut_lens, step_lens
+
+    for spec, P in CUT:
+        reqs = [(kernel_of(spec), n) for n in cut_lens(P)]
+        ln = plan(shim, reqs, P)
+        assert ln != plan(shim, reqs, P, whole=True) and ln[2][0][0] < P, (spec.name, P)
+    for spec, P in [c for c in CUT if c[0].name in ("gqa32x8d128", "gqa64x8d128", "mla64")]:
+        reqs = [(kernel_of(spec), n + 2) for n in step_lens(P)]  # the second of three steps
+        assert plan(shim, reqs, P)[2][0][0] < P, (spec.name, P)
+    for batch in BY_TIME:
+        reqs = [(kernel_of(spec), n) for spec, n in batch]
+        ln = plan(shim, reqs, 64)
+        assert ln[0] == SLOTS and ln != plan(shim, reqs, 64, whole=True)

@@ -14,15 +14,30 @@ from workloads.harness import to_device_u16
 pytestmark = pytest.mark.gpu
 
 LENS = [1, 31, 33, 65, 130, 257, 700]
+CUT = [(gqa(32, 8), 64), (gqa(16, 16), 64), (gqa(30, 6), 128), (gqa(32, 16, 64), 128), (gqa(64, 8), 64),
+       (gqa(32, 1), 512), (gqa(128, 2), 256), (gqa(256, 2), 192), (mla(16), 128), (mla(12), 256), (mla(20), 128),
+       (mla(64), 128), (mla(32), 192)]
 
 
-@pytest.mark.parametrize("model,page_tokens", [
-    (gqa(32, 8), 64), (gqa(16, 16), 64), (gqa(30, 6), 128), (gqa(32, 16, 64), 128), (gqa(64, 8), 64),
-    (gqa(32, 1), 512), (gqa(128, 2), 256), (gqa(256, 2), 192), (mla(16), 128), (mla(12), 256), (mla(20), 128),
-    (mla(64), 128), (mla(32), 192)], ids=lambda x: getattr(x, "name", x))
+def cut_lens(P):
+    """Contexts of more than a page (a batch with one-page contexts stays on
+    whole pages): test_cost_line.py checks that these are cut inside pages."""
+    return [P + 1, P + 31, P + P // 2, 2 * P - 1, 2 * P + 33, 3 * P + P // 2 + 3, 5 * P - 2, 700 + P]
+
+
+def step_lens(P):
+    return [2 * P - 1, 2 * P, 2 * P + P // 2 + 3, 5 * P - 2]
+
+
+BY_TIME = [[(gqa(40, 8), 8000), (mla(64), 4100), (mla(20), 1), (gqa(40, 8), 5003), (mla(20), 2501), (gqa(28, 4), 65)],
+           [(gqa(128, 1), 9000), (gqa(128, 2), 31), (gqa(128, 2), 8001), (gqa(64, 8), 7010), (gqa(128, 1), 64)]]
+
+
+@pytest.mark.parametrize("model,page_tokens", CUT, ids=lambda x: getattr(x, "name", x))
 def test_ranges_inside_pages(model, page_tokens):
     print(f"[case] {model.name} P{page_tokens}", flush=True)
     run([(model, n) for n in LENS], page_tokens, BAL, 0)
+    run([(model, n) for n in cut_lens(page_tokens)], page_tokens, BAL, 0)
 
 
 def test_models_of_different_blocks_in_one_launch():
@@ -31,10 +46,13 @@ def test_models_of_different_blocks_in_one_launch():
 
 @pytest.mark.parametrize("model,page_tokens", [(gqa(32, 8), 64), (gqa(64, 8), 64), (mla(16), 256), (mla(64), 128)],
                          ids=lambda x: getattr(x, "name", x))
-def test_fused_step_over_ranges_inside_pages(model, page_tokens):
-    """Contexts around page ends and in the middle of a page; the step and
-    the two calls it stands for run on two pools holding the same rows."""
-    lens = [page_tokens - 1, page_tokens, 2 * page_tokens + page_tokens // 2 + 3, 5 * page_tokens - 2]
+@pytest.mark.parametrize("first", [1, 2])
+def test_fused_step_over_ranges_inside_pages(model, page_tokens, first):
+    """Contexts around page ends and in the middle of a page, with a one-page
+    one (ranges of whole pages) and without; the step and the two calls it
+    stands for run on two pools holding the same rows."""
+    lens = step_lens(page_tokens)
+    lens[:2] = [first * page_tokens - 1, first * page_tokens]
     rng = np.random.default_rng(3)
     rows = [rng.standard_normal((n + 3, model.row_width), dtype=np.float32) for n in lens]
     bits = [(x.view(np.uint32) >> 16).astype(np.uint16) for x in rows]
@@ -140,4 +158,5 @@ def test_models_sharing_a_launch_by_time():
     cost, with and without sub-page blocks."""
     run([(gqa(40, 8), 6000), (mla(64), 2100), (mla(20), 1), (gqa(40, 8), 5003), (mla(20), 1501), (gqa(28, 4), 65)], 64,
         BAL, 0)
-    run([(gqa(128, 1), 9000), (gqa(128, 2), 31), (gqa(128, 2), 8001), (gqa(64, 8), 7010), (gqa(128, 1), 64)], 64, BAL, 0)
+    for batch in BY_TIME:
+        run(batch, 64, BAL, 0)
